@@ -8,17 +8,23 @@
 //    (x, u), the affine offset, and the zero-order hold over dt
 //    (A_d, B_d, w_d from the exponential of [[A, B, w], [0, 0, 0]] dt);
 //  - nlink_step_kernel: classical RK4 substeps of the nonlinear dynamics.
-// Inverse dynamics come from a recursive Newton-Euler pass over the chain
-// (O(N) per call): accelerations of the mass points outward, the force and
-// moment carried by each joint inward.  M(q) is N such passes with qd = 0 and
-// qdd = e_j (one per thread), C(q, qd) one pass with qdd = 0, M is factored
-// by Cholesky across the workgroup, and the Jacobian of the forward dynamics
-// follows from differentiating RNEA(q, qd, qdd(q, qd, tau)) = tau - b qd:
-// dqdd/dx_s = M^-1 (d(tau - b qd)/dx_s - dRNEA/dx_s |qdd fixed), the last
-// term a forward-mode dual-number pass per direction (one per thread).  The
-// zero-order hold works on the n x n state block (Phi and its integral)
-// rather than on the augmented matrix.  Everything runs in FP64 (the model
-// is tiny); outputs are written in the problem dtype.
+//
+// Both work in the absolute angles th_a = q_0 + .. + q_a (rates om_a, torque
+// on th_a: tau_a - tau_{a+1}), where the planar chain needs no recursion:
+//   sum_b W_ab (cos(th_a - th_b) al_b + sin(th_a - th_b) om_b^2)
+//     = (tau - b qd)_a - (tau - b qd)_{a+1},
+//   W_ab = l_a l_b sum_{i >= max(a, b)} m_i,
+// and qdd_a = al_a - al_{a-1}.  Lane r of each 16-lane row owns link r and
+// keeps row r of the mass matrix in registers; the other links' values reach
+// it by lane reads, and the matrix is eliminated by Gauss-Jordan steps in the
+// same registers (symmetric positive definite: no pivoting), so an evaluation
+// of the dynamics has no LDS access and no barrier.  What bounds both kernels
+// is the chain of dependent FP64 operations of one evaluation; the recursive
+// Newton-Euler passes, Cholesky and substitutions through LDS that this
+// replaced took 15 us per evaluation at 13 links (4 RK4 substeps 244 us,
+// linearization 83 us); see the kernels for the present figures.
+// Everything runs in FP64 (the model is tiny); outputs are written in the
+// problem dtype.
 #include <hip/hip_runtime.h>
 #include <math.h>
 
@@ -28,396 +34,381 @@ namespace empc {
 
 namespace {
 
-struct Dual {
-    double v, d;
+// 1 / x by the hardware estimate and two Newton steps (the estimate's
+// relative error of about 2^-23 is squared twice): within 1-2 units in the
+// last place, an eighth of the dependent instructions of a division.
+__device__ __forceinline__ double recip(double x) {
+    double r = __builtin_amdgcn_rcp(x);
+    r = fma(fma(-x, r, 1.0), r, r);
+    return fma(fma(-x, r, 1.0), r, r);
+}
+
+// Link r's part of the chain, r = lane mod 16 (every 16-lane row alike).
+// NB >= N: compile-time row length; links past N have W = 0 and a unit
+// diagonal, so they never couple to the others.
+template <int NB>
+struct Link {
+    int r;
+    bool in;       // r < N
+    double W[NB];  // l_r l_k sum of the masses from link max(r, k) on
+    double b;      // viscous damping (0 past N)
+
+    template <typename T>
+    __device__ __forceinline__ void load(int N, const T *mass, const T *len, double damping) {
+        r = threadIdx.x & 15;
+        in = r < N;
+        const double l = in ? (double)len[r] : 0.0;
+        const double mu = row_scan_down<double>(in ? (double)mass[r] : 0.0);
+        b = in ? damping : 0.0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k)
+            W[k] = l * lane_bcast<double>(l, k) * (k > r ? lane_bcast<double>(mu, k) : mu);
+    }
+    // torque on the absolute angle: t_r - t_{r+1} with t = tau - b qd
+    __device__ __forceinline__ double torque(double tau, double om) const {
+        const double t = in ? tau - b * (om - row_shift_up<double>(om, 1)) : 0.0;
+        return t - row_shift_down<double>(t, 1);
+    }
+    // row r of the mass matrix and the centripetal sum sum_k W sin om_k^2
+    __device__ __forceinline__ double row(double th, double om, double *a) const {
+        double s, c;
+        sincos(th, &s, &c);
+        const double o2 = om * om;
+        double h = 0.0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const double ck = lane_bcast<double>(c, k), sk = lane_bcast<double>(s, k);
+            a[k] = W[k] * (c * ck + s * sk);
+            h += W[k] * (s * ck - c * sk) * lane_bcast<double>(o2, k);
+            if (k == r && !in) a[k] = 1.0;
+        }
+        return h;
+    }
+    // absolute accelerations: Gauss-Jordan on (mass matrix | torque)
+    __device__ __forceinline__ double acceleration(double th, double om, double tau) const {
+        double a[NB];
+        double y = torque(tau, om);
+        y -= row(th, om, a);
+        double own = 0.0;  // reciprocal of this row's pivot
+#pragma unroll
+        for (int j = 0; j < NB; ++j) {
+            const double ip = recip(lane_bcast<double>(a[j], j));
+            const double f = r == j ? 0.0 : a[j] * ip;
+            own = r == j ? ip : own;
+#pragma unroll
+            for (int k = j + 1; k < NB; ++k) a[k] -= f * lane_bcast<double>(a[k], j);
+            y -= f * lane_bcast<double>(y, j);
+        }
+        return y * own;
+    }
 };
-__device__ inline Dual operator+(Dual a, Dual b) { return {a.v + b.v, a.d + b.d}; }
-__device__ inline Dual operator-(Dual a, Dual b) { return {a.v - b.v, a.d - b.d}; }
-__device__ inline Dual operator*(Dual a, Dual b) { return {a.v * b.v, a.v * b.d + a.d * b.v}; }
-__device__ inline Dual operator*(double s, Dual a) { return {s * a.v, s * a.d}; }
-// sine and cosine of an angle whose value's sine and cosine are known
-__device__ inline void sincos_at(double, double s0, double c0, double *s, double *c) {
-    *s = s0;
-    *c = c0;
-}
-__device__ inline void sincos_at(Dual a, double s0, double c0, Dual *s, Dual *c) {
-    *s = {s0, c0 * a.d};
-    *c = {c0, -s0 * a.d};
-}
-template <typename S>
-__device__ inline S make(double v, double d);
-template <>
-__device__ inline double make<double>(double v, double) { return v; }
-template <>
-__device__ inline Dual make<Dual>(double v, double d) { return {v, d}; }
 
-// Inverse dynamics of the planar chain without gravity: joint torques that
-// produce accelerations qdd at (q, qd), the viscous damping excluded.
-// Mass point i moves with a_i = a_{i-1} + l_i (alpha_i u_i^perp - omega_i^2
-// u_i), u_i = (cos phi_i, sin phi_i), phi/omega/alpha the absolute angle,
-// rate and acceleration of link i; joint i carries the force f_i =
-// sum_{j>=i} m_j a_j and the moment tau_i = tau_{i+1} + l_i u_i x f_i.
-// Loops run to NLINK_MAX with the links past N skipped, so that the
-// per-link arrays live in registers (every index a compile-time constant).
-// sphi, cphi: sine and cosine of the absolute angles at q (a table shared
-// by all passes at the same q); a dual q carries its directional part into
-// them by the chain rule.
-template <typename S, typename QV, typename DV, typename AV>
-__device__ __forceinline__ void rnea(int N, const double *mass, const double *len,
-                                     const double *sphi, const double *cphi, const QV &q,
-                                     const DV &qd, const AV &qdd, S *tau) {
-    S ux[NLINK_MAX], uy[NLINK_MAX], ax[NLINK_MAX], ay[NLINK_MAX];
-    S phi = make<S>(0, 0), om = make<S>(0, 0), al = make<S>(0, 0);
-    S px = make<S>(0, 0), py = make<S>(0, 0);
-#pragma unroll
-    for (int i = 0; i < NLINK_MAX; ++i) {
-        if (i < N) {
-            phi = phi + q(i);
-            om = om + qd(i);
-            al = al + qdd(i);
-            S sn, c;
-            sincos_at(phi, sphi[i], cphi[i], &sn, &c);
-            const S w2 = om * om;
-            px = px + len[i] * (make<S>(0, 0) - al * sn - w2 * c);
-            py = py + len[i] * (al * c - w2 * sn);
-            ux[i] = c;
-            uy[i] = sn;
-            ax[i] = px;
-            ay[i] = py;
-        }
-    }
-    S fx = make<S>(0, 0), fy = make<S>(0, 0), t = make<S>(0, 0);
-#pragma unroll
-    for (int i = NLINK_MAX - 1; i >= 0; --i) {
-        if (i < N) {
-            fx = fx + mass[i] * ax[i];
-            fy = fy + mass[i] * ay[i];
-            t = t + len[i] * (ux[i] * fy - uy[i] * fx);
-            tau[i] = t;
-        }
-    }
+// ---------------------------------------------------------------------------
+// Linearization.  Eight wavefronts: the first three each run the dynamics
+// (the same values) and build one of the right-hand sides' blocks, the rest
+// is 32 x 32 matrix products on the FP64 matrix cores, a 16 x 16 tile of a
+// product per wavefront, two products at a time.
+constexpr int LIN_THREADS = 512;
+constexpr int LDM = 34;             // row stride of the 32 x 32 matrices in LDS
+constexpr int MSZ = 32 * LDM;
+constexpr int LDR = 50;             // row stride of the right-hand sides [16][48]
+constexpr int HOLD_BLOCKS = 4;      // blocks of four terms above the leading three
+
+typedef double v4d __attribute__((ext_vector_type(4)));
+
+// 1 / (k + 1)!, k = 0..18
+__device__ constexpr double hold_coef(int k) {
+    double f = 1.0;
+    for (int i = 2; i <= k + 1; ++i) f *= (double)i;
+    return 1.0 / f;
 }
 
-// Cholesky factor of the N x N matrix A (row-major, LDS) by every thread of
-// the workgroup: column j is scaled by the threads of its rows, then the
-// trailing block is updated in parallel; the strictly lower part of A
-// receives L, dg the diagonal of L.  Must be reached by every thread.
-__device__ void cholesky_par(int N, double *A, double *dg) {
-    const int t = threadIdx.x;
-    for (int j = 0; j < N; ++j) {
-        const double d = sqrt(A[j * N + j]);
-        if (t == j) dg[j] = d;
-        if (t > j && t < N) A[t * N + j] /= d;
-        __syncthreads();
-        const int rem = N - j - 1;
-        for (int e = t; e < rem * rem; e += blockDim.x) {
-            const int i = j + 1 + e / rem, k = j + 1 + e % rem;
-            if (k <= i) A[i * N + k] -= A[i * N + j] * A[k * N + j];
-        }
-        __syncthreads();
-    }
-}
-
-// (L L^T)^-1 r with thread t < N holding r_t in yt (returned as y_t); each
-// step's pivot goes through sh (N doubles of LDS).  Every thread.
-__device__ double chol_solve_par(int N, const double *L, const double *dg, double yt,
-                                 double *sh) {
-    const int t = threadIdx.x;
-    for (int j = 0; j < N; ++j) {  // L z = r
-        if (t == j) {
-            yt /= dg[j];
-            sh[j] = yt;
-        }
-        __syncthreads();
-        if (t > j && t < N) yt -= L[t * N + j] * sh[j];
-    }
-    for (int j = N - 1; j >= 0; --j) {  // L^T y = z
-        if (t == j) {
-            yt /= dg[j];
-            sh[j] = yt;
-        }
-        __syncthreads();
-        if (t < j) yt -= L[j * N + t] * sh[j];
-    }
-    return yt;
-}
-
-// (L L^T)^-1 r for one right-hand side held in registers by one thread (L,
-// dg in LDS, read by every thread at the same address).
-__device__ __forceinline__ void chol_solve_regs(int N, const double *L, const double *dg,
-                                                double *y) {
-#pragma unroll
-    for (int i = 0; i < NLINK_MAX; ++i) {
-        if (i < N) {
-            double s = y[i];
-#pragma unroll
-            for (int k = 0; k < NLINK_MAX; ++k)
-                if (k < i) s -= L[i * N + k] * y[k];
-            y[i] = s / dg[i];
-        }
-    }
-#pragma unroll
-    for (int i = NLINK_MAX - 1; i >= 0; --i) {
-        if (i < N) {
-            double s = y[i];
-#pragma unroll
-            for (int k = 0; k < NLINK_MAX; ++k)
-                if (k > i && k < N) s -= L[k * N + i] * y[k];
-            y[i] = s / dg[i];
-        }
-    }
-}
-
-// Forward dynamics qdd = M^-1 (tau - C - b qd) at (q, qd) (LDS arrays) by the
-// workgroup: threads 0..N-1 build M's columns, thread N the bias C, all of
-// them factor M; the result qdd (LDS, N doubles) and the factor (Msh, dg)
-// are left for the caller.  Must be reached by every thread.
-// Sine and cosine of the absolute angles q_0 + .. + q_i, thread i (LDS).
-// Must be reached by every thread.
-__device__ void angle_table(int N, const double *q, double *sphi, double *cphi) {
-    const int t = threadIdx.x;
-    if (t < N) {
-        double phi = 0.0;
-        for (int i = 0; i <= t; ++i) phi += q[i];
-        sincos(phi, &sphi[t], &cphi[t]);
-    }
-    __syncthreads();
-}
-
-// (inlined into its callers, so that its LDS arrays are addressed as LDS)
-__device__ __forceinline__ void forward_dynamics(int N, const double *mass, const double *len,
-                                                 double b,
-                                 const double *q, const double *qd, const double *tau,
-                                 double *Msh, double *dg, double *sh, double *sphi,
-                                 double *cphi, double *qdd) {
-    const int tid = threadIdx.x;
-    auto zero = [](int) { return 0.0; };
-    auto qv = [&](int i) { return q[i]; };
-    double rhs = 0.0;
-    angle_table(N, q, sphi, cphi);
-    if (tid < N) {
-        double col[NLINK_MAX];
-        rnea<double>(N, mass, len, sphi, cphi, qv, zero,
-                     [&](int i) { return i == tid ? 1.0 : 0.0; }, col);
-#pragma unroll
-        for (int i = 0; i < NLINK_MAX; ++i)
-            if (i < N) Msh[i * N + tid] = col[i];
-    } else if (tid == N) {
-        double col[NLINK_MAX];
-        rnea<double>(N, mass, len, sphi, cphi, qv, [&](int i) { return qd[i]; }, zero, col);
-#pragma unroll
-        for (int i = 0; i < NLINK_MAX; ++i)
-            if (i < N) qdd[i] = tau[i] - col[i] - b * qd[i];
-    }
-    __syncthreads();
-    if (tid < N) rhs = qdd[tid];
-    cholesky_par(N, Msh, dg);
-    rhs = chol_solve_par(N, Msh, dg, rhs, sh);
-    __syncthreads();  // every read of sh done before qdd (maybe the same caller buffer) changes
-    if (tid < N) qdd[tid] = rhs;
-    __syncthreads();
-}
-
-constexpr int LIN_THREADS = 256;
-
-// C = A B for n x n matrices in LDS (row-major, leading dimension n), all
-// threads, a 2 x 2 block of C per thread
-__device__ void matmul_lds(int n, const double *A, const double *B, double *C) {
-    const int h = (n + 1) / 2;
-    for (int e = threadIdx.x; e < h * h; e += blockDim.x) {
-        const int i = 2 * (e / h), j = 2 * (e % h);
-        const bool i1 = i + 1 < n, j1 = j + 1 < n;
-        double c00 = 0.0, c01 = 0.0, c10 = 0.0, c11 = 0.0;
-        for (int k = 0; k < n; ++k) {
-            const double a0 = A[i * n + k], a1 = i1 ? A[(i + 1) * n + k] : 0.0;
-            const double b0 = B[k * n + j], b1 = j1 ? B[k * n + j + 1] : 0.0;
-            c00 += a0 * b0;
-            c01 += a0 * b1;
-            c10 += a1 * b0;
-            c11 += a1 * b1;
-        }
-        C[i * n + j] = c00;
-        if (j1) C[i * n + j + 1] = c01;
-        if (i1) C[(i + 1) * n + j] = c10;
-        if (i1 && j1) C[(i + 1) * n + j + 1] = c11;
-    }
-    __syncthreads();
-}
-
-constexpr int NS_MAX = 2 * NLINK_MAX;  // states
-
-template <typename T>
+// 13 links: 83 us with recursive dual-number passes and VALU products,
+// 16 us in this form (error of A_d, B_d, w_d against 64-bit references: 1.3e-13
+// before, 1.1e-14 now, FP64 robot).
+template <typename T, int NB>
 __global__ __launch_bounds__(LIN_THREADS) void nlink_linearize_kernel(
     int N, const T *__restrict__ mass_in, const T *__restrict__ len_in, double b, double dt,
     const T *__restrict__ x_in, const T *__restrict__ u_in, T *__restrict__ Ad,
     T *__restrict__ Bd, T *__restrict__ wd) {
-    __shared__ double mass[NLINK_MAX], len[NLINK_MAX], x[NS_MAX], u[NLINK_MAX];
-    __shared__ double Msh[NLINK_MAX * NLINK_MAX], dg[NLINK_MAX], sh[NLINK_MAX];
-    __shared__ double sphi[NLINK_MAX], cphi[NLINK_MAX], qdd0[NLINK_MAX];
-    __shared__ double J[3 * NLINK_MAX][NLINK_MAX];  // dqdd / d(q, qd, tau), column s
-    __shared__ double Y[NS_MAX * NS_MAX], G[NS_MAX * NS_MAX], W[NS_MAX * NS_MAX];
-    __shared__ double Ph[NS_MAX * NS_MAX], F[NS_MAX * (NLINK_MAX + 1)];
-    __shared__ int s_scale;
+    // Y = A h and its powers; H: the right-hand sides, then the polynomial;
+    // F: [B | w].  Rows and columns past n stay zero.
+    __shared__ double Y[MSZ], Y2[MSZ], Y3[MSZ], Y4[MSZ], H[MSZ], F[MSZ];
+    __shared__ double qdd[16], dotp[3][16], colsum[32];
+    static_assert(16 * LDR <= MSZ, "right-hand sides fit");
     const int tid = threadIdx.x, n = 2 * N, m = N;
-    if (tid < N) {
-        mass[tid] = (double)mass_in[tid];
-        len[tid] = (double)len_in[tid];
-        u[tid] = (double)u_in[tid];
-    }
-    if (tid < n) x[tid] = (double)x_in[tid];
-    __syncthreads();
-    forward_dynamics(N, mass, len, b, x, x + N, u, Msh, dg, sh, sphi, cphi, qdd0);
-    // direction s < 2N: state x_s; 2N <= s < 3N: torque s - 2N.  The
-    // Jacobian of RNEA(q, qd, qdd0) in direction s by one dual-number pass.
-    if (tid < 3 * N) {
-        double y[NLINK_MAX];
-        if (tid < n) {
-            Dual t[NLINK_MAX];
-            rnea<Dual>(
-                N, mass, len, sphi, cphi, [&](int i) { return Dual{x[i], i == tid ? 1.0 : 0.0}; },
-                [&](int i) { return Dual{x[N + i], N + i == tid ? 1.0 : 0.0}; },
-                [&](int i) { return Dual{qdd0[i], 0.0}; }, t);
+    const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    double iv[NB];  // row r of dqdd / d(torque on the absolute angles)
+    double xs = 0.0;  // this lane's column entry of (q, qd, tau) for the offset
+    if (wave < 3) {
+        Link<NB> L;
+        L.load(N, mass_in, len_in, b);
+        const int r = L.r;
+        const double q = L.in ? (double)x_in[r] : 0.0, qd = L.in ? (double)x_in[N + r] : 0.0;
+        const double u = L.in ? (double)u_in[r] : 0.0;
+        xs = wave == 0 ? q : wave == 1 ? qd : u;
+        const double th = row_scan_up<double>(q), om = row_scan_up<double>(qd);
+        double s, c;
+        sincos(th, &s, &c);
+        double a[NB];
+        double y = L.torque(u, om);
+        y -= L.row(th, om, a);
+        // in-place Gauss-Jordan inverse; each row is scaled by its pivot last
+        double own = 0.0;
 #pragma unroll
-            for (int i = 0; i < NLINK_MAX; ++i)
-                if (i < N) y[i] = -t[i].d - (N + i == tid ? b : 0.0);
-        } else {
+        for (int j = 0; j < NB; ++j) {
+            const double ip = recip(lane_bcast<double>(a[j], j));
+            const double f = r == j ? 0.0 : a[j] * ip;
+            own = r == j ? ip : own;
 #pragma unroll
-            for (int i = 0; i < NLINK_MAX; ++i) y[i] = i == tid - n ? 1.0 : 0.0;
+            for (int k = 0; k < NB; ++k)
+                if (k != j) a[k] -= f * lane_bcast<double>(a[k], j);
+            a[j] = r == j ? 1.0 : -f;
         }
-        chol_solve_regs(N, Msh, dg, y);
+        double al = 0.0;
 #pragma unroll
-        for (int i = 0; i < NLINK_MAX; ++i)
-            if (i < N) J[tid][i] = y[i];
+        for (int k = 0; k < NB; ++k) {
+            a[k] *= own;
+            al += a[k] * lane_bcast<double>(y, k);
+        }
+        // rows of differences: al_r - al_{r-1} = qdd_r
+#pragma unroll
+        for (int k = 0; k < NB; ++k) iv[k] = a[k] - row_shift_up<double>(a[k], 1);
+        const double qa = al - row_shift_up<double>(al, 1);
+        if (wave == 0 && grp == 0) qdd[r] = qa;
+        // Row r of the right-hand sides of M dal/d(.) = ..., in the relative
+        // coordinates.  With D_ab = W_ab (cos om_b^2 - sin al_b):
+        //  q_s:  -sum_{c < s} D_ac for s <= a, sum_{c >= s} D_ac above;
+        //  qd_s: -sum_{c >= s} 2 W_ac sin om_c, and the damping of joint s;
+        //  tau_s: the unit torque of joint s.
+        double e[NB];
+        const double o2 = om * om;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            const double ck = lane_bcast<double>(c, k), sk = lane_bcast<double>(s, k);
+            const double sn = s * ck - c * sk, cs = c * ck + s * sk;
+            e[k] = wave == 0 ? L.W[k] * (cs * lane_bcast<double>(o2, k) -
+                                         sn * lane_bcast<double>(al, k))
+                             : -2.0 * L.W[k] * sn * lane_bcast<double>(om, k);
+        }
+        double pre[NB];  // sums over c < s
+        double t = 0.0;
+#pragma unroll
+        for (int k = 0; k < NB; ++k) {
+            pre[k] = t;
+            t += e[k];
+        }
+        t = 0.0;
+#pragma unroll
+        for (int k = NB - 1; k >= 0; --k) {
+            t += e[k];  // sum over c >= k
+            const double unit = L.in ? (k == r ? 1.0 : k == r + 1 && k < N ? -1.0 : 0.0) : 0.0;
+            const double v = wave == 0 ? (k <= r ? -pre[k] : t)
+                                       : wave == 1 ? t - L.b * unit : unit;
+            if (grp == 0) H[r * LDR + 16 * wave + k] = v;
+        }
+    } else {
+        // the other wavefronts clear the matrices
+        for (int e = tid - 192; e < MSZ; e += LIN_THREADS - 192)
+            Y[e] = Y2[e] = Y3[e] = Y4[e] = F[e] = 0.0;
+    }
+    __syncthreads();
+    // J block of wavefront w < 3: (rows of differences) x (its right-hand
+    // sides), 16 x 16; row i is qdd_i, column s the s-th q, qd or tau
+    if (wave < 3) {
+        v4d acc = {0, 0, 0, 0};
+#pragma unroll
+        for (int k0 = 0; k0 < 16; k0 += 4) {
+            double av = 0.0;
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                if (k0 + g < NB) av = grp == g ? iv[k0 + g < NB ? k0 + g : 0] : av;
+            const double bv = k0 + grp < NB && col < NB ? H[(k0 + grp) * LDR + 16 * wave + col]
+                                                        : 0.0;
+            acc = __builtin_amdgcn_mfma_f64_16x16x4f64(av, bv, acc, 0, 0, 0);
+        }
+        double *to = wave == 2 ? F : Y;
+        const int c0 = wave == 1 ? N : 0;
+        const double scale = wave == 2 ? 1.0 : dt;
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int i = grp + 4 * v;
+            if (i < N && col < N) to[(N + i) * LDM + c0 + col] = acc[v] * scale;
+            const double d = row_scan_up<double>(acc[v] * xs);  // lane 15 of the row: the sum
+            if (col == 15) dotp[wave][i] = d;
+        }
+    } else if (wave == 3) {
+        if (lane < N) Y[lane * LDM + N + lane] = dt;  // position rows of A: qd
     }
     __syncthreads();
     // f(x, u) ~ f0 + A (x' - x) + B (u' - u): A = [[0, I], [Jq, Jqd]],
-    // B = [[0], [Ju]], offset w = f0 - A x - B u (position rows: 0).
-    // F holds [B | w] (n x (m + 1)); Y = A dt first, scaled below.
-    const int m1 = m + 1;
-    for (int e = tid; e < n * n; e += blockDim.x) {
-        const int i = e / n, j = e % n;
-        Y[e] = (i < N ? (j == N + i ? 1.0 : 0.0) : J[j][i - N]) * dt;
-    }
-    for (int e = tid; e < n * m1; e += blockDim.x) {
-        const int i = e / m1, j = e % m1;
-        double v = 0.0;
-        if (i >= N) {
-            const int k = i - N;
-            if (j < m) {
-                v = J[n + j][k];
-            } else {
-                v = qdd0[k];
-                for (int s2 = 0; s2 < n; ++s2) v -= J[s2][k] * x[s2];
-                for (int s2 = 0; s2 < m; ++s2) v -= J[n + s2][k] * u[s2];
-            }
-        }
-        F[e] = v;
+    // B = [[0], [Ju]], offset w = f0 - A x - B u (position rows: 0)
+    if (tid < N) F[(N + tid) * LDM + m] = qdd[tid] - (dotp[0][tid] + dotp[1][tid] + dotp[2][tid]);
+    if (tid >= 64 && tid < 96) {
+        double cs = 0.0;
+        for (int i = 0; i < n; ++i) cs += fabs(Y[i * LDM + tid - 64]);
+        colsum[tid - 64] = cs;
     }
     __syncthreads();
     // Zero-order hold: Phi = exp(A dt), Gamma = int_0^dt exp(A s) ds, then
-    // A_d = Phi, [B_d w_d] = Gamma [B w].  Scaling and squaring on
-    // h = dt / 2^s with |A h|_1 <= 1/4: G = sum_k (A h)^k / (k+1)! by a
-    // degree-14 Horner scheme (truncation below 1e-20), Phi(h) = I + A h G,
-    // Gamma(h) = h G; each squaring Gamma <- Gamma + Phi Gamma,
-    // Phi <- Phi Phi.  The column sums of |Y| and their maximum by the first
-    // wavefront.
-    if (tid < 64) {
-        double c = 0.0;
-        if (tid < n)
-            for (int i = 0; i < n; ++i) c += fabs(Y[i * n + tid]);
+    // A_d = Phi, [B_d w_d] = Gamma [B w].  Scaling and squaring on h = dt /
+    // 2^sc with |A h|_1 <= 1: G = sum_{k <= 18} (A h)^k / (k+1)! (truncation
+    // below 1e-18) in blocks of four powers (Paterson-Stockmeyer: 7 products
+    // where Horner takes 18), Phi(h) = I + A h G, V = h G [B w]; each
+    // squaring V <- V + Phi V, Phi <- Phi Phi.
+    double cmax = colsum[lane & 31];
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) c = fmax(c, __shfl_xor(c, o, 64));
-        if (tid == 0) {
-            int sc = 0;
-            while (c > 0.25 && sc < 64) {
-                c *= 0.5;
-                ++sc;
-            }
-            s_scale = sc;
-        }
+    for (int o = 16; o >= 1; o >>= 1) cmax = fmax(cmax, __shfl_xor(cmax, o, 64));
+    int sc = 0;
+    while (cmax > 1.0 && sc < 66) {
+        cmax *= 0.5;
+        ++sc;
     }
-    __syncthreads();
-    const int sc = s_scale;
+    sc = __builtin_amdgcn_readfirstlane(sc);
     const double scl = ldexp(1.0, -sc), h = dt * scl;
-    for (int e = tid; e < n * n; e += blockDim.x) {
-        Y[e] *= scl;
-        G[e] = (e / n == e % n ? 1.0 : 0.0) + Y[e] / 15.0;
+    for (int e = tid; e < MSZ; e += LIN_THREADS) Y[e] *= scl;
+    __syncthreads();
+    const int prod = wave >> 2, ti = (wave >> 1) & 1, tj = wave & 1;
+    const bool live = 16 * ti < n && 16 * tj < n;  // tiles past the states stay zero
+    // this wavefront's tile of A B: lane holds rows 16 ti + grp + 4 v, column
+    // 16 tj + col
+    auto product = [&](const double *A, const double *B) {
+        v4d acc = {0, 0, 0, 0};
+        if (live) {
+            const double *ap = A + (16 * ti + col) * LDM + grp, *bp = B + grp * LDM + 16 * tj + col;
+            for (int k0 = 0; k0 < n; k0 += 4)
+                acc = __builtin_amdgcn_mfma_f64_16x16x4f64(ap[k0], bp[k0 * LDM], acc, 0, 0, 0);
+        }
+        return acc;
+    };
+    const int e0 = (16 * ti + grp) * LDM + 16 * tj + col;  // element of v: + 4 v LDM
+    auto store = [&](double *to, v4d x) {
+        if (live) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) to[e0 + 4 * v * LDM] = x[v];
+        }
+    };
+    auto eye = [&](int v) {
+        const int i = 16 * ti + grp + 4 * v;
+        return i == 16 * tj + col && i < n ? 1.0 : 0.0;
+    };
+    if (prod == 0) store(Y2, product(Y, Y));
+    __syncthreads();
+    if (prod == 0)
+        store(Y3, product(Y2, Y));
+    else
+        store(Y4, product(Y2, Y2));
+    // H = c16 I + c17 Y + c18 Y^2 (its right-hand sides have been read)
+    if (prod == 0) {
+        v4d x = {0, 0, 0, 0};
+#pragma unroll
+        for (int v = 0; v < 4; ++v)
+            x[v] = hold_coef(16) * eye(v) + hold_coef(17) * Y[e0 + 4 * v * LDM] +
+                   hold_coef(18) * Y2[e0 + 4 * v * LDM];
+#pragma unroll
+        for (int v = 0; v < 4; ++v) H[e0 + 4 * v * LDM] = x[v];
     }
     __syncthreads();
-    for (int k = 13; k >= 1; --k) {  // G <- I + Y G / (k + 1)
-        matmul_lds(n, Y, G, W);
-        for (int e = tid; e < n * n; e += blockDim.x)
-            G[e] = (e / n == e % n ? 1.0 : 0.0) + W[e] / (double)(k + 1);
+#pragma unroll
+    for (int blk = HOLD_BLOCKS - 1; blk >= 0; --blk) {  // H <- H Y^4 + block
+        v4d x = {0, 0, 0, 0};
+        if (prod == 0) {
+            x = product(H, Y4);
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+                x[v] += hold_coef(4 * blk) * eye(v) + hold_coef(4 * blk + 1) * Y[e0 + 4 * v * LDM] +
+                        hold_coef(4 * blk + 2) * Y2[e0 + 4 * v * LDM] +
+                        hold_coef(4 * blk + 3) * Y3[e0 + 4 * v * LDM];
+        }
+        __syncthreads();
+        if (prod == 0) store(H, x);
         __syncthreads();
     }
-    matmul_lds(n, Y, G, W);
-    for (int e = tid; e < n * n; e += blockDim.x) {
-        Ph[e] = (e / n == e % n ? 1.0 : 0.0) + W[e];
-        G[e] *= h;
-    }
-    __syncthreads();
-    for (int r = 0; r < sc; ++r) {
-        matmul_lds(n, Ph, G, W);  // Phi Gamma
-        for (int e = tid; e < n * n; e += blockDim.x) G[e] += W[e];
+    double *Ph = Y2, *V = Y3;  // the powers are no longer needed
+    {
+        v4d x = prod == 0 ? product(Y, H) : product(H, F);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) x[v] = prod == 0 ? x[v] + eye(v) : h * x[v];
         __syncthreads();
-        matmul_lds(n, Ph, Ph, W);
-        for (int e = tid; e < n * n; e += blockDim.x) Ph[e] = W[e];
+        store(prod == 0 ? Ph : V, x);
         __syncthreads();
     }
-    for (int e = tid; e < n * n; e += blockDim.x) Ad[e] = (T)Ph[e];
-    for (int e = tid; e < n * m1; e += blockDim.x) {
-        const int i = e / m1, j = e % m1;
-        double v = 0.0;
-        for (int k = 0; k < n; ++k) v += G[i * n + k] * F[k * m1 + j];
-        if (j < m)
-            Bd[i * m + j] = (T)v;
-        else
-            wd[i] = (T)v;
+    for (int s = 0; s < sc; ++s) {
+        v4d x = product(Ph, prod == 0 ? Ph : V);
+        if (prod == 1) {
+#pragma unroll
+            for (int v = 0; v < 4; ++v) x[v] += V[e0 + 4 * v * LDM];
+        }
+        __syncthreads();
+        store(prod == 0 ? Ph : V, x);
+        __syncthreads();
+    }
+    for (int e = tid; e < n * 32; e += LIN_THREADS) {
+        const int i = e / 32, j = e % 32;
+        if (j < n) Ad[i * n + j] = (T)Ph[i * LDM + j];
+        if (j < m) Bd[i * m + j] = (T)V[i * LDM + j];
+        if (j == m) wd[i] = (T)V[i * LDM + j];
     }
 }
 
 constexpr int STEP_THREADS = 64;
 
-// Classical RK4 over dt in `sub` substeps, tau held; one wavefront.
-template <typename T>
+// Classical RK4 over dt in `sub` substeps, tau held; one wavefront (its four
+// 16-lane rows compute the same values).  The increments of the absolute
+// angles and rates are accumulated and turned back into relative ones at
+// the end.  13 links, 4 substeps: 244 us -> 31 us, 1.9 us per evaluation of
+// the dynamics.
+template <typename T, int NB>
 __global__ __launch_bounds__(STEP_THREADS) void nlink_step_kernel(
     int N, const T *__restrict__ mass_in, const T *__restrict__ len_in, double b, double dt,
     int sub, const T *x_in, const T *__restrict__ u_in, T *x_out) {
-    __shared__ double mass[NLINK_MAX], len[NLINK_MAX], tau[NLINK_MAX];
-    __shared__ double st[NS_MAX];
-    __shared__ double Msh[NLINK_MAX * NLINK_MAX], dg[NLINK_MAX], sh[NLINK_MAX], qdd[NLINK_MAX];
-    __shared__ double sphi[NLINK_MAX], cphi[NLINK_MAX];
-    const int tid = threadIdx.x, n = 2 * N;
-    if (tid < N) {
-        mass[tid] = (double)mass_in[tid];
-        len[tid] = (double)len_in[tid];
-        tau[tid] = (double)u_in[tid];
-    }
-    // thread i < n keeps state i (y), its RK4 sum (acc) in registers
-    double y = tid < n ? (double)x_in[tid] : 0.0;
+    Link<NB> L;
+    L.load(N, mass_in, len_in, b);
+    const double tau = L.in ? (double)u_in[L.r] : 0.0;
+    const double q = L.in ? (double)x_in[L.r] : 0.0, qd = L.in ? (double)x_in[N + L.r] : 0.0;
+    const double th0 = row_scan_up<double>(q), om0 = row_scan_up<double>(qd);
+    double dth = 0.0, dom = 0.0;
     const double hs = dt / sub;
     for (int s = 0; s < sub; ++s) {
-        double acc = 0.0;
-        if (tid < n) st[tid] = y;
-        __syncthreads();
+        double ath = 0.0, aom = 0.0, oth = dth, oom = dom;
         // the four stages share one inlined copy of the dynamics; weights
         // 1, 2, 2, 1 and next-stage offsets 0.5, 0.5, 1
 #pragma unroll 1
         for (int stage = 0; stage < 4; ++stage) {
-            forward_dynamics(N, mass, len, b, st, st + N, tau, Msh, dg, sh, sphi, cphi, qdd);
-            // k = [qd; qdd] at the stage state; next stage state y + off h k
-            double k = 0.0;
-            if (tid < n) {
-                k = tid < N ? st[N + tid] : qdd[tid - N];
-                acc += (stage == 0 || stage == 3 ? 1.0 : 2.0) * k;
-            }
-            __syncthreads();
-            if (tid < n && stage < 3) st[tid] = y + (stage == 2 ? 1.0 : 0.5) * hs * k;
-            __syncthreads();
+            const double th = th0 + oth, kth = om0 + oom;
+            const double kom = L.acceleration(th, kth, tau);
+            const double w = stage == 0 || stage == 3 ? 1.0 : 2.0;
+            ath += w * kth;
+            aom += w * kom;
+            const double off = (stage == 2 ? 1.0 : 0.5) * hs;
+            oth = dth + off * kth;
+            oom = dom + off * kom;
         }
-        if (tid < n) y += hs / 6.0 * acc;
+        dth += hs / 6.0 * ath;
+        dom += hs / 6.0 * aom;
     }
-    if (tid < n) x_out[tid] = (T)y;
+    const double nq = q + (dth - row_shift_up<double>(dth, 1));
+    const double nqd = qd + (dom - row_shift_up<double>(dom, 1));
+    if (threadIdx.x < 16 && L.in) {
+        x_out[L.r] = (T)nq;
+        x_out[N + L.r] = (T)nqd;
+    }
+}
+
+// instance of the smallest even row length that holds N links
+template <typename F>
+hipError_t by_links(int N, F &&go) {
+    switch ((N + 1) / 2) {
+        case 1: return go(std::integral_constant<int, 2>());
+        case 2: return go(std::integral_constant<int, 4>());
+        case 3: return go(std::integral_constant<int, 6>());
+        case 4: return go(std::integral_constant<int, 8>());
+        case 5: return go(std::integral_constant<int, 10>());
+        case 6: return go(std::integral_constant<int, 12>());
+        case 7: return go(std::integral_constant<int, 14>());
+        default: return go(std::integral_constant<int, 16>());
+    }
 }
 
 }  // namespace
@@ -425,16 +416,20 @@ __global__ __launch_bounds__(STEP_THREADS) void nlink_step_kernel(
 template <typename T>
 hipError_t launch_nlink_linearize(int N, const T *mass, const T *len, double b, double dt,
                                   const T *x, const T *u, T *Ad, T *Bd, T *wd, hipStream_t s) {
-    hipLaunchKernelGGL(nlink_linearize_kernel<T>, dim3(1), dim3(LIN_THREADS), 0, s, N, mass, len,
-                       b, dt, x, u, Ad, Bd, wd);
-    return hipGetLastError();
+    return by_links(N, [&](auto nb) {
+        hipLaunchKernelGGL((nlink_linearize_kernel<T, decltype(nb)::value>), dim3(1),
+                           dim3(LIN_THREADS), 0, s, N, mass, len, b, dt, x, u, Ad, Bd, wd);
+        return hipGetLastError();
+    });
 }
 template <typename T>
 hipError_t launch_nlink_step(int N, const T *mass, const T *len, double b, double dt, int sub,
                              const T *x, const T *u, T *x_next, hipStream_t s) {
-    hipLaunchKernelGGL(nlink_step_kernel<T>, dim3(1), dim3(STEP_THREADS), 0, s, N, mass, len, b,
-                       dt, sub, x, u, x_next);
-    return hipGetLastError();
+    return by_links(N, [&](auto nb) {
+        hipLaunchKernelGGL((nlink_step_kernel<T, decltype(nb)::value>), dim3(1),
+                           dim3(STEP_THREADS), 0, s, N, mass, len, b, dt, sub, x, u, x_next);
+        return hipGetLastError();
+    });
 }
 template hipError_t launch_nlink_linearize<float>(int, const float *, const float *, double,
                                                   double, const float *, const float *, float *,
