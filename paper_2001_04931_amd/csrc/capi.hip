@@ -143,7 +143,12 @@ bool quadratic_refine(const empc_problem *P) {
     if (P->model != EMPC_LINEAR || P->qb || P->Q || P->R || P->Qf) return false;
     const int pm = P->p * P->m;
     if (pm > QP_REFINE_MAX_PM) return false;
-    return qp_form_bytes(P->n, P->T, pm) + (size_t)pm * pm * esize(P) <= QP_REFINE_MAX_BYTES;
+    // eight FP64 forms count beside the responses: the line between the two
+    // ways to refine lies where it was when the form was summed from eight
+    // partial ones, so that no problem changes its way
+    const size_t partial = ((size_t)pm * pm * 8 + 31) / 32 * 32 * sizeof(double);
+    return qp_form_bytes(P->n, P->T, pm) + partial + (size_t)pm * pm * esize(P) <=
+           QP_REFINE_MAX_BYTES;
 }
 
 // qp: room for the quadratic form of refinement (the static solve, which

@@ -50,3 +50,56 @@ def test_robot_every_row_length(oracle_lib, E, N):
     np.testing.assert_allclose(xn.cpu().numpy(),
                                oracle_lib.nlink_rk4(mass, length, b, x, u, 0.01, 3),
                                rtol=1e-11, atol=1e-12)
+
+
+def random_linear(n, m, T, p, seed):
+    rng = np.random.default_rng(seed)
+    A = rng.normal(0, 1, (n, n))
+    A *= 0.97 / max(abs(np.linalg.eigvals(A)))
+    return W.Problem(model=W.LINEAR, n=n, m=m, T=T, p=p, Ad=A, Bd=rng.normal(0, 1, (n, m)),
+                     wd=rng.normal(0, 0.1, n), q=rng.uniform(0.5, 2, n),
+                     r=rng.uniform(0.01, 0.1, m), qf=rng.uniform(0, 1, n),
+                     x_goal=rng.normal(0, 1, n), u_goal=rng.normal(0, 0.2, m),
+                     u_min=-np.ones(m), u_max=np.ones(m))
+
+
+# (states, inputs, horizon, knots): knot parameters 1, 15, 16, 17, 64, 65, 144,
+# 160 (the last of the LDS factor), 161 (the first of the global one), and
+# states at the ends of the response kernel's row lengths
+@pytest.mark.parametrize("n,m,T,p", [(2, 1, 1, 1), (3, 3, 9, 5), (16, 4, 12, 4), (17, 17, 7, 1),
+                                     (32, 8, 20, 8), (33, 13, 11, 5), (64, 9, 66, 16),
+                                     (65, 16, 30, 10), (80, 23, 8, 7)])
+def test_convex_sizes(oracle_lib, E, n, m, T, p):
+    """P, q, c to FP64 rounding of the oracle's (1e-11 of the largest entry) and
+    the minimizer by its optimality conditions (1e-9 of the gradient's scale:
+    the solver stops at rounding level)."""
+    from oracle import convex as C
+
+    prob = random_linear(n, m, T, p, 100 * n + m)
+    x0 = W.draw_x0(n, 7, scale=2.0)
+    cs = E.ConvexSolver(E.DeviceProblem(prob, F64))
+    z, J, info = (v.cpu().numpy() for v in cs.solve(dev(x0)))
+    Po, qo, co = C.qp_form(prob, x0)
+    np.testing.assert_allclose(cs.P.cpu().numpy(), Po, rtol=1e-11, atol=1e-11 * np.abs(Po).max())
+    np.testing.assert_allclose(cs.q.cpu().numpy(), qo, rtol=1e-11, atol=1e-11 * np.abs(qo).max())
+    np.testing.assert_allclose(cs.c.item(), co, rtol=1e-11)
+    lo, hi = C.knot_bounds(prob)
+    g = 2 * (Po @ z + qo)
+    assert info[1] == 1 and np.all(z >= lo) and np.all(z <= hi)
+    assert np.abs(z - np.clip(z - g, lo, hi)).max() < 1e-9 * max(1.0, np.abs(qo).max())
+    np.testing.assert_allclose(J[0], C.qp_cost(Po, qo, co, z), rtol=1e-10)
+
+
+def test_convex_pivots_outside_the_plain_range(E):
+    """Weights of 1e210 make pivots whose reciprocals leave the fast square
+    root's range: the factorization is repeated with the library's functions.
+    Unbounded, so z = -P^-1 q (condition below 1e5: 1e-9)."""
+    prob = random_linear(4, 3, 20, 5, 12)
+    prob.u_min, prob.u_max = np.full(3, -1e250), np.full(3, 1e250)
+    for k in ("q", "r", "qf"):
+        setattr(prob, k, getattr(prob, k) * 1e210)
+    cs = E.ConvexSolver(E.DeviceProblem(prob, F64), max_iter=3)
+    z, _, _ = cs.solve(dev(np.full(4, 0.3)))
+    P, q = cs.P.cpu().numpy() * 1e-210, cs.q.cpu().numpy() * 1e-210
+    assert np.all(np.isfinite(P))
+    np.testing.assert_allclose(z.cpu().numpy(), -np.linalg.solve(P, q), rtol=1e-9, atol=1e-9)
