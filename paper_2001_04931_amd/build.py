@@ -27,6 +27,7 @@ DEVICE_FLAGS = ["-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops"]
 # next step's MFMAs and by VALU cost code, and the AGPR form would force
 # copies between the two register files on every step.
 FILE_FLAGS = {"rollout_linear_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
+              "adjoint_linear_f32.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"],
               "batched.hip": ["-mllvm", "-amdgpu-mfma-vgpr-form"]}
 COMMON = ["-O3", "-std=c++17", "-fPIC", f"--offload-arch={ARCH}", "-Wall",
           "-Wno-unused-function", "-Wno-unused-result"]

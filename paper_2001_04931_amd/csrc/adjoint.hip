@@ -461,10 +461,26 @@ size_t grad_smem_bytes(int model, int n, int m, int T, int p, size_t esize) {
     return grad_plan(model, n, m, T, p).total * esize;
 }
 
+template <>
+hipError_t launch_adjoint_linear<float>(const ProbView<float> &, const float *, const float *,
+                                        int64_t, int64_t, float *, float *, int, float, float *,
+                                        float *, hipStream_t, bool *);
+template <>
+hipError_t launch_adjoint_linear<double>(const ProbView<double> &, const double *,
+                                         const double *, int64_t, int64_t, double *, double *,
+                                         int, double, double *, double *, hipStream_t, bool *);
+
 template <typename T>
 hipError_t launch_grad(const ProbView<T> &P, int model, const T *x0, const T *knots, int64_t ncand,
                        int64_t ld, T *dJ, T *cost, int refine_steps, T lr, T *knots_io,
                        T *cost_io, hipStream_t s) {
+    if (model == EMPC_LINEAR) {
+        bool taken = false;
+        const hipError_t e = launch_adjoint_linear<T>(P, x0, knots, ncand, ld, dJ, cost,
+                                                      refine_steps, lr, knots_io, cost_io, s,
+                                                      &taken);
+        if (taken || e != hipSuccess) return e;
+    }
     const GradPlan G = grad_plan(model, P.n, P.m, P.Tn, P.p);
     const size_t bytes = G.total * sizeof(T);
     auto go = [&](auto kernel) {

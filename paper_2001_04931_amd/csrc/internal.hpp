@@ -436,6 +436,14 @@ hipError_t launch_grad(const ProbView<T> &P, int model, const T *x0, const T *kn
                        int64_t ld, T *dJ, T *cost, int refine_steps, T lr, T *knots_io,
                        T *cost_io, hipStream_t s);
 
+// The linear model's adjoint and refinement on the matrix cores (per dtype in
+// adjoint_linear_f32.hip / _f64.hip); *taken false: nothing was launched, the
+// call is launch_grad's own.
+template <typename T>
+hipError_t launch_adjoint_linear(const ProbView<T> &P, const T *x0, const T *knots, int64_t ncand,
+                                 int64_t ld, T *dJ, T *cost, int steps, T lr, T *knots_io,
+                                 T *cost_io, hipStream_t s, bool *taken);
+
 // LDS bytes of the adjoint kernel; the kernel needs n <= 64 (linear) or
 // d <= 64 (chain) and at most MAX_GRAD_LDS bytes.
 size_t grad_smem_bytes(int model, int n, int m, int T, int p, size_t esize);

@@ -103,3 +103,74 @@ def test_convex_pivots_outside_the_plain_range(E):
     P, q = cs.P.cpu().numpy() * 1e-210, cs.q.cpu().numpy() * 1e-210
     assert np.all(np.isfinite(P))
     np.testing.assert_allclose(z.cpu().numpy(), -np.linalg.solve(P, q), rtol=1e-9, atol=1e-9)
+
+
+# (states, inputs, horizon, knots, candidates, dtype): every state-tile count
+# and input-tile count of the matrix-core adjoint, ragged candidate tiles, one
+# knot, a knot per step, horizons whose states do not fit in LDS (FP64 50 steps
+# and up at two tiles), and more input than state tiles (the per-candidate
+# kernel)
+ADJOINT = [
+    (1, 1, 1, 1, 1, F64), (3, 2, 9, 9, 17, F64), (16, 16, 20, 4, 16, F32), (17, 5, 21, 6, 15, F64),
+    (28, 14, 60, 10, 33, F64), (32, 32, 12, 3, 40, F32), (33, 9, 25, 5, 31, F64),
+    (48, 20, 14, 2, 16, F64), (40, 40, 18, 4, 20, F32), (64, 16, 30, 1, 18, F64),
+    (64, 32, 60, 3, 16, F32), (64, 40, 11, 11, 5, F64), (28, 14, 300, 7, 48, F32),
+    (5, 20, 10, 3, 7, F64),
+]
+
+
+@pytest.mark.parametrize("box", [False, True])
+@pytest.mark.parametrize("n,m,T,p,ncand,dtype", ADJOINT)
+def test_linear_adjoint_shapes(oracle_lib, E, n, m, T, p, ncand, dtype, box):
+    """Costs and gradients against the FP64 oracle's: FP64 1e-9 of a column's
+    largest entry; FP32 the method's 1e-4 (cost) and 2e-3 (gradient), the
+    rounding of T dependent steps."""
+    npd = np.float64 if dtype == F64 else np.float32
+    prob = random_linear(n, m, T, p, 10 * n + m)
+    if box:
+        prob.x_min, prob.x_max = prob.x_goal - 0.3, prob.x_goal + 0.3
+        prob.qb = np.linspace(0.5, 2.0, n)
+    prob = prob.cast(npd)
+    ld = ncand + 3
+    x0 = W.draw_x0(n, 3).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 5, ld=ld).astype(npd).astype(np.float64)
+    dp, K = E.DeviceProblem(prob, dtype), dev(knots, dtype)
+    dJ, cost = torch.full_like(K, float("nan")), dev(np.full(ncand, np.nan), dtype)
+    E.empc_grad(dp, dev(x0, dtype), K, ncand, ld, dJ, cost)
+    want, wcost = oracle_lib.grad(prob, x0, knots, ncand)
+    got = dJ.cpu().numpy().astype(np.float64)
+    assert np.all(np.isnan(got[:, ncand:]))  # nothing stored past the candidates
+    err = np.abs(got[:, :ncand] - want[:, :ncand]).max(axis=0)
+    scale = np.abs(want[:, :ncand]).max(axis=0)
+    tg, tc = (1e-9, 1e-10) if dtype == F64 else (2e-3, 1e-4)
+    assert (err <= tg * scale + 1e-30).all()
+    np.testing.assert_allclose(cost.cpu().numpy(), wcost, rtol=tc)
+    # refinement on the same tiles: a few Adam steps against the oracle's
+    if dtype == F64:
+        wk, wc = oracle_lib.refine(prob, x0, knots, wcost, lr=0.01, steps=3)
+        C = dev(wcost, dtype)
+        E.empc_refine(dp, dev(x0, dtype), K, ncand, ld, C, 0.01, 3)
+        np.testing.assert_allclose(C.cpu().numpy(), wc, rtol=1e-9)
+        np.testing.assert_allclose(K.cpu().numpy()[:, :ncand], wk[:, :ncand], rtol=0, atol=1e-9)
+
+
+def test_linear_adjoint_blocks_equal_kept_states(E):
+    """More candidate tiles than the chip holds with every state in LDS: the
+    states are recomputed in blocks, by the same steps from the same stored
+    states, so the first candidates' gradients are the same bits as in a
+    small call that keeps them all; a candidate's NaN stays its own."""
+    prob = W.linear_chain(14, 50, 10, seed=1).cast(np.float32)
+    dp = E.DeviceProblem(prob, F32)
+    n1, n2 = 64, 16 * 256 + 40
+    x0 = dev(W.draw_x0(prob.n, 1), F32)
+    K = dev(W.draw_knots(prob, n2, 2), F32)
+    K[3, 5] = float("nan")
+    out = []
+    for nc in (n1, n2):
+        dJ, cost = torch.zeros_like(K), torch.zeros(n2, device="cuda")
+        E.empc_grad(dp, x0, K, nc, n2, dJ, cost)
+        out.append((dJ[:, :n1].cpu(), cost[:n1].cpu()))
+    for a, b in zip(*out):
+        assert torch.equal(a.nan_to_num(123.0), b.nan_to_num(123.0))
+        bad = torch.isnan(a).reshape(-1, n1).any(0)
+        assert bad[5] and bad.sum() == 1
