@@ -584,11 +584,10 @@ def nonsmooth_workload(E, W, ticks=100, with_cpu=True):
     flop = ga.pop * full_weight_flop_per_candidate(prob.n, prob.m, prob.T)
     r = {"rollouts_per_s": rate, "latency_ms": lat_summary(lats), "ticks": ticks,
          "dtype": "f32", "autotuned": tuned, "final_best_cost": costs[-1],
-         "roofline": kernel_roofline(prof, flop, PEAK_FP32_VALU,
-                                     "roll_linear_valu<full>"
-                                     if tuned["rollout_form"] in (E.RF_VALU256, E.RF_VALU64)
-                                     else "roll_linear_full_rows",
-                                     bound="valu")}
+         "roofline": kernel_roofline(prof, flop, PEAK_FP32_VALU, "roll_linear_valu<full>",
+                                     bound="valu")
+         if tuned["rollout_form"] in (E.RF_VALU256, E.RF_VALU64)
+         else kernel_roofline(prof, flop, PEAK_FP32_MFMA, "roll_linear_full")}
     if with_cpu:
         jobs = [closed_loop_job(prob, W.dataclasses.replace(ga, generations=5), 1, s, 1e-3)
                 for s in range(1 + host_cores())]

@@ -1,24 +1,22 @@
 // Linear-model rollout + cost with full weights Q, R, Qf (eq. 3 in general
-// form), 16 lanes per candidate (gfx950).
+// form) on the matrix cores (gfx950).
 //
-// With one candidate per lane (rollout_valu.hpp) a population of a few
-// thousand is only a few dozen wavefronts, each stepping through n (n + m)
-// + n^2 multiply-adds per step in sequence.  Here a 16-lane row of a
-// wavefront carries one candidate (4 per wavefront, 16 per workgroup of
-// 256): lane r owns state rows r, r + 16, .. (J of them, n <= 16 J) and
-// inputs r, r + 16, .. (JM, m <= 16 JM).  A_d, B_d, Q and R sit in LDS
-// (shared by the workgroup's candidates, rows padded to an odd stride so
-// the row's 16 lanes hit 16 banks); the state goes through LDS once per
-// step: every lane writes its rows, then reads the whole vector back (a
-// row lies inside one wavefront, whose LDS operations complete in order,
-// so no barrier is needed), and one pass over it gives both the next state
-// rows (A_d x + the knot term) and the rows of Q (x - g) for the stage cost
-// of x.  The knot term is precomputed per knot (V_a = B_d U_a + w_d, the
-// lane's rows), the input cost of a knot segment is summed in closed form
-// (u is affine in c there): nseg e0^T R e0 + 2 C1 e0^T R du + C2 du^T R du
-// with e0 = U_a - u_g, du = U_b - U_a, each lane taking its inputs' rows of
-// R.  The terminal weight Qf is read from global memory once.  The row's
-// partial costs are summed over its 16 lanes at the end.
+// A tile of 16 candidates runs on NT = ceil(n / 16) wavefronts, wavefront w
+// owning state rows 16w .. 16w+15, in the layout, K order and exchange of the
+// M-split rollout (rollout_linear.hpp).  The weight product Q x_k is a second
+// contraction over the same B operands as A_d x_k: its 4 NT MFMAs per step
+// depend on nothing in the step, so they run while the new state's sums
+// finish and go through LDS.  The stage cost adds (x - g)^T (Q x - Q g) with
+// Q g precomputed.  The input cost of a knot segment is closed form in
+// E_a = U_a - u_g and R E_a, one product per knot:
+//   S00 E_a^T R E_a + 2 S01 E_a^T R E_b + S11 E_b^T R E_b
+// with the sums of (1-c)^2, c (1-c), c^2 over the segment.  The terminal
+// weight's operands are loaded after the last step.
+//
+// The step's chain of MFMAs bounds it (8 NT of them, 32 cycles each in FP32).
+// On the vector ALUs, 16 lanes per candidate with A_d and Q read from LDS in
+// every step, the 7-DoF chain (4096 candidates, 50 steps, FP32) took 40 us;
+// here 16 us; 32 DoF 273 and 55 us; FP64 42 and 27, 362 and 94 us (2048).
 #pragma once
 #include <math.h>
 
@@ -26,249 +24,240 @@
 
 namespace empc {
 
-constexpr int FULL_ROWS_NMAX = 64;  // states of the 16-lane full-weight form
-constexpr int FULL_ROWS_MMAX = 32;  // inputs
-
-// LDS layout of the form (elements of T): A [nr][sa], B [nr][sb], Q [nr][sa],
-// R [m][sr], the goals x_g [n] and u_g [m], the workgroup's states xs
-// [16][nr] and knots us [16][2][m]; nr = 16 J rows, the rows past n zero, so
-// that the step loop runs with no guard (a padding row stays at zero).
-struct FullRowsLds {
-    int sa, sb, sr;
-    int oA, oB, oQ, oR, oG, oUg, oX, oU, total;
-};
-__host__ __device__ inline FullRowsLds full_rows_lds(int n, int m, int J) {
-    FullRowsLds L;
-    const int nr = 16 * J;
-    L.sa = n | 1;
-    L.sb = m | 1;
-    L.sr = m | 1;
-    L.oA = 0;
-    L.oB = L.oA + nr * L.sa;
-    L.oQ = L.oB + nr * L.sb;
-    L.oR = L.oQ + nr * L.sa;
-    L.oG = L.oR + m * L.sr;
-    L.oUg = L.oG + n;
-    L.oX = L.oUg + m;
-    L.oU = L.oX + 16 * nr;
-    L.total = L.oU + 16 * 2 * m;
-    return L;
-}
-
-template <typename T, int J, int JM, bool BOX>
-__global__ __launch_bounds__(256) void roll_linear_full_rows(ProbView<T> P,
-                                                             const T *__restrict__ x0,
-                                                             const T *__restrict__ knots,
-                                                             int64_t ld, int64_t ncand,
-                                                             T *__restrict__ cost) {
-    extern __shared__ __align__(16) unsigned char full_smem[];
-    T *sm = (T *)full_smem;
-    const int n = P.n, m = P.m, p = P.p, Tn = P.Tn;
-    constexpr int NR = 16 * J;
-    const FullRowsLds L = full_rows_lds(n, m, J);
-    T *sA = sm + L.oA, *sB = sm + L.oB, *sQ = sm + L.oQ, *sR = sm + L.oR;
-    T *sG = sm + L.oG, *sUg = sm + L.oUg;
-    for (int i = threadIdx.x; i < n; i += blockDim.x) sG[i] = P.xg ? P.xg[i] : (T)0;
-    for (int i = threadIdx.x; i < m; i += blockDim.x) sUg[i] = P.ug ? P.ug[i] : (T)0;
-    // stage A_d, B_d, Q, R (a diagonal given as a vector goes on the diagonal)
-    for (int e = threadIdx.x; e < NR * n; e += blockDim.x) {
-        const int i = e / n, j = e % n;
-        const bool in = i < n;
-        sA[i * L.sa + j] = in ? P.Ad[e] : (T)0;
-        sQ[i * L.sa + j] = !in ? (T)0 : P.Qm ? P.Qm[e] : (i == j ? P.q[i] : (T)0);
-    }
-    for (int e = threadIdx.x; e < NR * m; e += blockDim.x)
-        sB[(e / m) * L.sb + e % m] = e < n * m ? P.Bd[e] : (T)0;
-    for (int e = threadIdx.x; e < m * m; e += blockDim.x) {
-        const int i = e / m, j = e % m;
-        sR[i * L.sr + j] = P.Rm ? P.Rm[e] : (i == j ? P.r[i] : (T)0);
-    }
-    __syncthreads();
-    const int r = threadIdx.x & 15, slot = threadIdx.x >> 4;  // lane in row, row in workgroup
-    const int64_t cand0 = (int64_t)blockIdx.x * 16;
-    if (cand0 + (threadIdx.x >> 6) * 4 >= ncand) return;  // whole wavefront past the end
-    const int64_t cand = cand0 + slot;
+// LV: live K slices of a single M-tile (states 4 v .. 4 v + 3 of slice v; 4
+// with more M-tiles): FP64 n = 4, 256 candidates, 50 steps 25.4 us with all
+// four slices, 15.5 us with one.
+template <typename T, int NT, int NU, bool BOX, int LV = 4>
+__global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
+                                                            const T *__restrict__ x0,
+                                                            const T *__restrict__ knots,
+                                                            int64_t ld, int64_t ncand,
+                                                            T *__restrict__ cost) {
+    typedef typename Mfma<T>::v4 v4;
+    constexpr int UT = (NU + 3) / 4, UW = (UT + NT - 1) / NT;  // input tiles: in all, per wavefront
+    __shared__ v4 xs[2][NT][64];
+    __shared__ T part[NT][16];
+    const int lane = threadIdx.x & 63;
+    const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & 15, grp = lane >> 4;
+    const int64_t cand = xcd_swizzle(blockIdx.x, gridDim.x) * 16 + col;
     const bool valid = cand < ncand;
-    const int64_t cc = valid ? cand : ncand - 1;  // loads stay in bounds
-    T *xs = sm + L.oX + slot * NR;
-    T *ua = sm + L.oU + slot * 2 * m, *ub = ua + m;
+    const int64_t cand_c = valid ? cand : ncand - 1;
+    const int n = P.n, m = P.m, p = P.p, Tn = P.Tn;
+    const int arow = 16 * w + Mfma<T>::mstate(col);
 
-    // the lane's rows: goal, disturbance, box
-    T g[J], w[J], lo[J], hi[J], qb[J], sbw[J];
+    // knots a, b = a + 1 and a + 2 while segment a runs: lane (grp, col) of
+    // slice s holds input 4 s + grp (padded inputs meet zero operands)
+    T Ka[NU], Kb[NU], Kn[NU];
+    auto load_knot = [&](int j, T *U) {
+        const int kc = j < p ? j : p - 1;
 #pragma unroll
-    for (int t = 0; t < J; ++t) {
-        const int i = r + 16 * t;
-        const bool in = i < n;
-        g[t] = (in && P.xg) ? P.xg[i] : (T)0;
-        w[t] = (in && P.wd) ? P.wd[i] : (T)0;
-        lo[t] = (BOX && in) ? P.xlo[i] : (T)0;
-        hi[t] = (BOX && in) ? P.xhi[i] : (T)0;
-        qb[t] = (BOX && in) ? P.qb[i] : (T)0;
-        sbw[t] = (BOX && in && P.sb) ? P.sb[i] : (T)0;
+        for (int s = 0; s < NU; ++s) {
+            const int i = 4 * s + grp;
+            U[s] = knots[(int64_t)(kc * m + (i < m ? i : m - 1)) * ld + cand_c];
+        }
+    };
+    load_knot(0, Ka);
+    load_knot(1, Kb);
+    // operands by slot i (M-tile t = (w + i) mod NT); full or diagonal weights
+    auto q_at = [&](int row, int kk) { return P.Qm ? P.Qm[row * n + kk] : row == kk ? P.q[row] : (T)0; };
+    T aX[4 * NT], aQ[4 * NT], aU[NU], aR[UW][NU], Ug[NU];
+#pragma unroll
+    for (int i = 0; i < NT; ++i)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int kk = 16 * ((w + i) % NT) + Mfma<T>::row(grp, v);
+            const bool in = arow < n && kk < n;
+            aX[4 * i + v] = in ? P.Ad[arow * n + kk] : (T)0;
+            aQ[4 * i + v] = in ? q_at(arow, kk) : (T)0;
+        }
+#pragma unroll
+    for (int s = 0; s < NU; ++s) {
+        const int j = 4 * s + grp;
+        aU[s] = arow < n && j < m ? P.Bd[arow * m + j] : (T)0;
+        Ug[s] = j < m && P.ug ? P.ug[j] : (T)0;
+#pragma unroll
+        for (int u = 0; u < UW; ++u) {
+            const int row = 16 * (w + NT * u) + Mfma<T>::mstate(col);
+            aR[u][s] = row >= m || j >= m ? (T)0
+                       : P.Rm             ? P.Rm[row * m + j]
+                       : row == j         ? P.r[row]
+                                          : (T)0;
+        }
     }
-    T gu[JM];
+    v4 X, Wd, Xg, Lo, Hi, Pn = {0, 0, 0, 0}, Cn = {0, 0, 0, 0};
 #pragma unroll
-    for (int t = 0; t < JM; ++t) {
-        const int i = r + 16 * t;
-        gu[t] = (i < m && P.ug) ? P.ug[i] : (T)0;
+    for (int v = 0; v < 4; ++v) {
+        const int row = 16 * w + Mfma<T>::row(grp, v);
+        const bool in = row < n;
+        X[v] = in ? x0[row] : (T)0;
+        Wd[v] = in && P.wd ? P.wd[row] : (T)0;
+        Xg[v] = in && P.xg ? P.xg[row] : (T)0;
+        Lo[v] = BOX && in ? P.xlo[row] : (T)-1;  // padding rows: around their zero state
+        Hi[v] = BOX && in ? P.xhi[row] : (T)1;
     }
-    // knots a (ua) and a+1 (ub) of the candidate in LDS, the lane's inputs
-    // loaded by the lane; knot a+2 is loaded into registers (pre) when
-    // segment a starts and stored to LDS when it ends, so the load's
-    // latency hides behind the segment's steps
-    T pre[JM];
-    auto fetch_knot = [&](int kn) {
-        const int kc = kn < p ? kn : p - 1;
+    // all of the model is waited for here, before the step loop's prefetches
+    __builtin_amdgcn_s_waitcnt(VMCNT0);
+    // this wavefront's rows of M V over all M-tiles (own tile first), from
+    // `start`, even and odd slices in two chains
+    auto contract = [&](const T *op, const v4 *V, v4 start) {
+        v4 acc[2] = {start, v4{0, 0, 0, 0}};
 #pragma unroll
-        for (int t = 0; t < JM; ++t) {
-            const int i = r + 16 * t;
-            pre[t] = i < m ? knots[(int64_t)(kc * m + i) * ld + cc] : (T)0;
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int v = 0; v < LV; ++v)
+                acc[v & 1] = Mfma<T>::op(op[4 * i + v], V[i][v], acc[v & 1]);
+        return LV == 1 ? acc[0] : acc[0] + acc[1];
+    };
+    // stored own tile -> every tile, by slot
+    auto gather = [&](int b, v4 *V) {
+        V[0] = X;
+        if (NT == 1) return;
+        lds_barrier();
+#pragma unroll
+        for (int i = 1; i < NT; ++i) V[i] = xs[b][(w + i) % NT][lane];
+    };
+    auto response = [&](const T *U) {
+        v4 V[2] = {Wd, v4{0, 0, 0, 0}};
+#pragma unroll
+        for (int s = 0; s < NU; ++s) V[s & 1] = Mfma<T>::op(aU[s], U[s], V[s & 1]);
+        return V[0] + V[1];
+    };
+    // R (U - u_g), rows of this wavefront's input tiles
+    auto r_times = [&](const T *U, v4 *RE) {
+#pragma unroll
+        for (int u = 0; u < UW; ++u) {
+            v4 V[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
+#pragma unroll
+            for (int s = 0; s < NU; ++s) V[s & 1] = Mfma<T>::op(aR[u][s], U[s] - Ug[s], V[s & 1]);
+            RE[u] = V[0] + V[1];
         }
     };
-    auto store_knot = [&](T *dst) {
+    // the inputs of this wavefront's tile u, register v (slice 4 (w + NT u) + v)
+    auto input_of = [&](const T *U, int u, int v) -> T {
+        T e = 0;
 #pragma unroll
-        for (int t = 0; t < JM; ++t) {
-            const int i = r + 16 * t;
-            if (i < m) dst[i] = pre[t];
-        }
+        for (int t = 0; t < UT; ++t)
+            if (4 * t + v < NU && t == w + NT * u) e = U[4 * t + v] - Ug[4 * t + v];
+        return e;
     };
-    // V = B_d U + w_d for the lane's rows from a knot in LDS (padding rows:
-    // zero rows of B_d, w = 0)
-    auto response = [&](const T *u, T *V) {
+    // Q g, from the goal published like a state
+    v4 V[NT], Qg;
+    {
+        const v4 x = X;
+        X = Xg;
+        if (NT > 1) xs[1][w][lane] = X;
+        gather(1, V);
+        Qg = contract(aQ, V, v4{0, 0, 0, 0});
+        X = x;
+        if (NT > 1) xs[0][w][lane] = X;
+    }
+    v4 Va = response(Ka), Vb = response(Kb), REa[UW], REb[UW];
+    r_times(Ka, REa);
+    r_times(Kb, REb);
+    const T inv_den = Tn > 1 ? (T)1 / (T)(Tn - 1) : (T)0;
+    T J = 0;
+    int buf = 0, k = 0;
+    for (int a = 0; a < p; ++a) {
+        // first step of segment a + 1
+        const int kend =
+            p == 1 || a == p - 1 ? Tn : ((a + 1) * (Tn - 1) + (p - 2)) / (p - 1);
+        load_knot(a + 2, Kn);
+        const v4 dV = Vb - Va;
+        T s00 = 0, s01 = 0, s11 = 0;
+        int rem = k * (p - 1) - a * (Tn - 1);
+        for (; k < kend; ++k, rem += p - 1) {
+            const T c = (T)rem * inv_den, d = (T)1 - c;
+            s00 += d * d;
+            s01 += c * d;
+            s11 += c * c;
+            gather(buf, V);
+            const v4 Xk = X;
+            X = contract(aX, V, Va + c * dV);
+            buf ^= 1;
+            if (NT > 1) xs[buf][w][lane] = X;
+            // stage cost of x_k (x_0 has none), beside the new state's way
+            const v4 QE = contract(aQ, V, -Qg);
+            T t = 0;
 #pragma unroll
-        for (int t = 0; t < J; ++t) V[t] = w[t];
-        for (int l = 0; l < m; ++l) {
-            const T ul = u[l];
+            for (int v = 0; v < 4; ++v) t += (Xk[v] - Xg[v]) * QE[v];
+            J = k > 0 ? J + t : (T)0;
+            if (BOX) {
 #pragma unroll
-            for (int t = 0; t < J; ++t) V[t] += sB[(r + 16 * t) * L.sb + l] * ul;
-        }
-    };
-    // the lane's share of the segment input cost
-    auto input_cost = [&](int nseg, T C1, T C2, bool last) -> T {
-        T s = 0;
-#pragma unroll
-        for (int t = 0; t < JM; ++t) {
-            const int i = r + 16 * t;
-            if (i < m) {
-                T re = 0, rd = 0;
-                for (int l = 0; l < m; ++l) {
-                    const T e0l = ua[l] - sUg[l];
-                    const T dul = last ? (T)0 : ub[l] - ua[l];
-                    re += sR[i * L.sr + l] * e0l;
-                    rd += sR[i * L.sr + l] * dul;
+                for (int v = 0; v < 4; ++v) {  // x_{k+1}'s
+                    Pn[v] += box_pen(X[v], Lo[v], Hi[v]);
+                    Cn[v] += box_out(X[v], Lo[v], Hi[v]);
                 }
-                const T e0 = ua[i] - gu[t], du = last ? (T)0 : ub[i] - ua[i];
-                s += (T)nseg * e0 * re + (T)2 * C1 * e0 * rd + C2 * du * rd;
             }
         }
-        return s;
-    };
-    // x_0 into LDS (padding rows: 0)
 #pragma unroll
-    for (int t = 0; t < J; ++t) {
-        const int i = r + 16 * t;
-        xs[i] = i < n ? x0[i] : (T)0;
-    }
-    fetch_knot(0);
-    store_knot(ua);
-    fetch_knot(1);
-    store_knot(ub);
-    // Q g for the lane's rows
-    T qg[J];
+        for (int u = 0; u < UW; ++u)
 #pragma unroll
-    for (int t = 0; t < J; ++t) qg[t] = 0;
-    for (int j = 0; j < n; ++j) {
-        const T gj = sG[j];
-#pragma unroll
-        for (int t = 0; t < J; ++t) qg[t] += sQ[(r + 16 * t) * L.sa + j] * gj;
-    }
-    T Va[J], Vb[J];
-    response(ua, Va);
-    response(ub, Vb);
-    T Jc = 0;
-    int a = 0, k = 0;
-    // knot position of step k kept incrementally: k (p-1) = a (T-1) + rem
-    const int den = Tn > 1 ? Tn - 1 : 1;
-    const T inv_den = (T)1 / (T)den;
-    int rem = 0;
-    for (; a < p; ++a) {
-        // steps of segment a: k .. kend-1 (first step of segment a+1:
-        // ceil((a+1)(T-1)/(p-1)))
-        const int kend = (p == 1 || a == p - 1) ? Tn : ((a + 1) * (Tn - 1) + (p - 2)) / (p - 1);
-        if (a + 2 < p + 1) fetch_knot(a + 2);
-        int nseg = 0;
-        T C1 = 0, C2 = 0;
-        for (; k < kend; ++k) {
-            const T c = (p > 1 && Tn > 1) ? (T)rem * inv_den : (T)0;
-            if (p > 1 && Tn > 1) {
-                rem += p - 1;
-                if (rem >= den) rem -= den;
+            for (int v = 0; v < 4; ++v) {
+                const T ea = input_of(Ka, u, v), eb = a == p - 1 ? (T)0 : input_of(Kb, u, v);
+                const T rb = a == p - 1 ? (T)0 : REb[u][v];
+                J += s00 * ea * REa[u][v] + (T)2 * s01 * ea * rb + s11 * eb * rb;
             }
-            C1 += c;
-            C2 += c * c;
-            ++nseg;
-            // one pass over x_k: next rows and (for k > 0) Q (x_k - g) rows
-            // (Q x - Q g, Q g precomputed), eight columns in flight
-            T xn[J], qe[J];
+        Va = Vb;
 #pragma unroll
-            for (int t = 0; t < J; ++t) {
-                xn[t] = Va[t] + c * (Vb[t] - Va[t]);
-                qe[t] = -qg[t];
-            }
-#pragma unroll 8
-            for (int j = 0; j < n; ++j) {
-                const T xj = xs[j];
+        for (int u = 0; u < UW; ++u) REa[u] = REb[u];
 #pragma unroll
-                for (int t = 0; t < J; ++t) {
-                    const int i = r + 16 * t;
-                    xn[t] += sA[i * L.sa + j] * xj;
-                    qe[t] += sQ[i * L.sa + j] * xj;
-                }
-            }
-            if (k > 0) {  // stage cost of x_k (padding rows add zero)
-#pragma unroll
-                for (int t = 0; t < J; ++t) {
-                    const T xi = xs[r + 16 * t];  // x_k, this lane's own row
-                    Jc += (xi - g[t]) * qe[t];
-                    if (BOX) Jc += qb[t] * box_pen(xi, lo[t], hi[t]) + sbw[t] * box_out(xi, lo[t], hi[t]);
-                }
-            }
-            // every lane of the row has read x_k (program order): store x_{k+1}
-#pragma unroll
-            for (int t = 0; t < J; ++t) xs[r + 16 * t] = xn[t];
+        for (int s = 0; s < NU; ++s) {
+            Ka[s] = Kb[s];
+            Kb[s] = Kn[s];
         }
-        Jc += input_cost(nseg, C1, C2, a == p - 1);
         if (a + 1 < p) {
-            // next segment: knot a+1 becomes the first, knot a+2 the second
-#pragma unroll
-            for (int t = 0; t < J; ++t) Va[t] = Vb[t];
-            // all lanes have used ua / ub (program order within the row)
-            for (int l = r; l < m; l += 16) ua[l] = ub[l];
-            store_knot(ub);
-            response(ub, Vb);
+            Vb = response(Kb);
+            r_times(Kb, REb);
         }
     }
-    // x_T: stage weight Q and terminal weight Qf (global), box
+    // x_T: stage and terminal weight
+    gather(buf, V);
+    const v4 QE = contract(aQ, V, -Qg);
+    v4 F = {0, 0, 0, 0};
+    if (P.Qfm) {
+        // (x - g) of every tile, published like a state
+        T aF[4 * NT];
 #pragma unroll
-    for (int t = 0; t < J; ++t) {
-        const int i = r + 16 * t;
-        if (i < n) {
-            T qf = 0, qs = 0;
-            for (int j = 0; j < n; ++j) {
-                const T ej = xs[j] - sG[j];
-                qs += sQ[i * L.sa + j] * ej;
-                qf += (P.Qfm ? P.Qfm[i * n + j] : ((i == j && P.qf) ? P.qf[i] : (T)0)) * ej;
+        for (int i = 0; i < NT; ++i)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int kk = 16 * ((w + i) % NT) + Mfma<T>::row(grp, v);
+                aF[4 * i + v] = arow < n && kk < n ? P.Qfm[arow * n + kk] : (T)0;
             }
-            const T xi = xs[i];
-            Jc += (xi - g[t]) * (qs + qf);
-            if (BOX) Jc += qb[t] * box_pen(xi, lo[t], hi[t]) + sbw[t] * box_out(xi, lo[t], hi[t]);
+        const v4 x = X;
+        X = X - Xg;
+        buf ^= 1;
+        if (NT > 1) xs[buf][w][lane] = X;
+        gather(buf, V);
+        F = contract(aF, V, v4{0, 0, 0, 0});
+        X = x;
+    } else if (P.qf) {
+#pragma unroll
+        for (int v = 0; v < 4; ++v) {
+            const int row = 16 * w + Mfma<T>::row(grp, v);
+            F[v] = row < n ? P.qf[row] * (X[v] - Xg[v]) : (T)0;
         }
     }
-    Jc += __shfl_xor(Jc, 8, 16);
-    Jc += __shfl_xor(Jc, 4, 16);
-    Jc += __shfl_xor(Jc, 2, 16);
-    Jc += __shfl_xor(Jc, 1, 16);
-    if (r == 0 && valid) cost[cand] = Jc;
+#pragma unroll
+    for (int v = 0; v < 4; ++v) {
+        J += (X[v] - Xg[v]) * (QE[v] + F[v]);
+        if (BOX) {
+            const int row = 16 * w + Mfma<T>::row(grp, v);
+            const bool in = row < n;
+            J += (in ? P.qb[row] : (T)0) * Pn[v] + (in && P.sb ? P.sb[row] : (T)0) * Cn[v];
+        }
+    }
+    J += __shfl_xor(J, 16, 64);
+    J += __shfl_xor(J, 32, 64);
+    if (NT > 1) {
+        if (grp == 0) part[w][col] = J;
+        lds_barrier();
+        J = part[0][col];
+#pragma unroll
+        for (int i = 1; i < NT; ++i) J += part[i][col];
+    }
+    if (w == 0 && grp == 0 && valid) cost[cand] = J;
 }
 
 }  // namespace empc

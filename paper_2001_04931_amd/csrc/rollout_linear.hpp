@@ -28,7 +28,6 @@
 #include <math.h>
 
 #include "internal.hpp"
-#include "rollout_full.hpp"
 #include "rollout_valu.hpp"
 
 namespace empc {
@@ -574,6 +573,10 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_split(ProbView<T> P,
                                               xcd_swizzle(blockIdx.x, gridDim.x));
 }
 
+}  // namespace empc
+#include "rollout_full.hpp"
+namespace empc {
+
 // Launch through hipExtLaunchKernelGGL when timing events are given: the
 // events are stamped by the kernel's own dispatch, with no extra stream
 // packets around it.
@@ -633,47 +636,39 @@ static hipError_t go_valu_full_n(const ProbView<T> &P, const T *x0, const T *kno
     if (P.n <= 8) return go_valu_full_m<T, 8, BOX>(P, x0, knots, ncand, ld, cost, s, ev, threads);
     return go_valu_full_m<T, 16, BOX>(P, x0, knots, ncand, ld, cost, s, ev, threads);
 }
-template <typename T, int J, int JM, bool BOX>
-static hipError_t go_full_rows_box(const ProbView<T> &P, const T *x0, const T *knots,
-                                   int64_t ncand, int64_t ld, T *cost, hipStream_t s,
-                                   const Events &ev) {
-    const size_t bytes = (size_t)full_rows_lds(P.n, P.m, J).total * sizeof(T);
-    auto kernel = roll_linear_full_rows<T, J, JM, BOX>;
-    if (bytes > 65536) {
-        const hipError_t e = hipFuncSetAttribute((const void *)kernel,
-                                                 hipFuncAttributeMaxDynamicSharedMemorySize,
-                                                 (int)bytes);
-        if (e != hipSuccess) return e;
-    }
-    return launch_timed(kernel, dim3((unsigned)((ncand + 15) / 16)), dim3(256), bytes, s, ev, P,
-                        x0, knots, ld, ncand, cost);
-}
-template <typename T, int J, bool BOX>
-static hipError_t go_full_rows_m(const ProbView<T> &P, const T *x0, const T *knots,
-                                 int64_t ncand, int64_t ld, T *cost, hipStream_t s,
-                                 const Events &ev) {
-    if (P.m <= 16) return go_full_rows_box<T, J, 1, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
-    return go_full_rows_box<T, J, 2, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
+template <typename T, int NT, bool BOX, int LV = 4>
+static hipError_t go_full_nu(const ProbView<T> &P, const T *x0, const T *knots, int64_t ncand,
+                             int64_t ld, T *cost, hipStream_t s, const Events &ev) {
+    auto go = [&](auto kernel) {
+        return launch_timed(kernel, dim3((unsigned)((ncand + 15) / 16)), dim3(64 * NT), 0, s, ev,
+                            P, x0, knots, ld, ncand, cost);
+    };
+    const int nu = (P.m + 3) / 4;
+    if (nu <= 1) return go(roll_linear_full<T, NT, 1, BOX, LV>);
+    if (nu <= 2) return go(roll_linear_full<T, NT, 2, BOX, LV>);
+    if (nu <= 4) return go(roll_linear_full<T, NT, 4, BOX, LV>);
+    return go(roll_linear_full<T, NT, 8, BOX, LV>);
 }
 template <typename T, bool BOX>
-static hipError_t go_full_rows(const ProbView<T> &P, const T *x0, const T *knots, int64_t ncand,
-                               int64_t ld, T *cost, hipStream_t s, const Events &ev) {
-    const int J = (P.n + 15) / 16;
-    if (J <= 1) return go_full_rows_m<T, 1, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
-    if (J <= 2) return go_full_rows_m<T, 2, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
-    if (J <= 3) return go_full_rows_m<T, 3, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
-    return go_full_rows_m<T, 4, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
+static hipError_t go_full(const ProbView<T> &P, const T *x0, const T *knots, int64_t ncand,
+                          int64_t ld, T *cost, hipStream_t s, const Events &ev) {
+    if (P.n <= 4) return go_full_nu<T, 1, BOX, 1>(P, x0, knots, ncand, ld, cost, s, ev);
+    if (P.n <= 8) return go_full_nu<T, 1, BOX, 2>(P, x0, knots, ncand, ld, cost, s, ev);
+    if (P.n <= 16) return go_full_nu<T, 1, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
+    if (P.n <= 32) return go_full_nu<T, 2, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
+    if (P.n <= 48) return go_full_nu<T, 3, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
+    return go_full_nu<T, 4, BOX>(P, x0, knots, ncand, ld, cost, s, ev);
 }
 
-// Full weights: the 16-lane row form (n <= 64, m <= 32) unless the VALU form
+// Full weights: the matrix-core form (n <= 64, m <= 32) unless the VALU form
 // (one lane per candidate, n, m <= 16) was chosen.
 template <typename T>
 static hipError_t go_valu_full(const ProbView<T> &P, const T *x0, const T *knots, int64_t ncand,
                                int64_t ld, T *cost, hipStream_t s, const Events &ev, int form) {
     const bool valu = (form == RF_VALU64 || form == RF_VALU256) && P.n <= 16 && P.m <= 16;
     if (!valu) {
-        if (P.qb) return go_full_rows<T, true>(P, x0, knots, ncand, ld, cost, s, ev);
-        return go_full_rows<T, false>(P, x0, knots, ncand, ld, cost, s, ev);
+        if (P.qb) return go_full<T, true>(P, x0, knots, ncand, ld, cost, s, ev);
+        return go_full<T, false>(P, x0, knots, ncand, ld, cost, s, ev);
     }
     const int threads = form == RF_VALU64 ? 64 : 256;
     if (P.qb) return go_valu_full_n<T, true>(P, x0, knots, ncand, ld, cost, s, ev, threads);

@@ -174,3 +174,50 @@ def test_linear_adjoint_blocks_equal_kept_states(E):
         assert torch.equal(a.nan_to_num(123.0), b.nan_to_num(123.0))
         bad = torch.isnan(a).reshape(-1, n1).any(0)
         assert bad[5] and bad.sum() == 1
+
+
+def spd(n, rng):
+    Q, _ = np.linalg.qr(rng.normal(0, 1, (n, n)))
+    return (Q * np.geomspace(1.0, 0.05, n)) @ Q.T
+
+
+# (states, inputs, horizon, knots, candidates): state counts at both ends of
+# every live-slice and tile count, input counts at the ends of the slice
+# counts (and more input than state tiles), one knot, one step, a knot per step
+FULL = [
+    (1, 1, 1, 1, 1), (4, 2, 9, 3, 17), (5, 20, 12, 4, 16), (8, 4, 20, 20, 33), (9, 5, 15, 2, 15),
+    (16, 8, 21, 6, 48), (16, 32, 8, 3, 5), (17, 9, 13, 4, 31), (32, 16, 25, 1, 18),
+    (33, 17, 18, 5, 16), (48, 1, 30, 10, 40), (49, 32, 11, 11, 7), (64, 32, 40, 7, 65),
+]
+
+
+@pytest.mark.parametrize("weights", ["QRQf", "Q", "R", "Qf"])
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("n,m,T,p,ncand", FULL)
+def test_full_weights_shapes(oracle_lib, E, n, m, T, p, ncand, dtype, weights):
+    """Costs with full weights against the FP64 oracle's, with the state box
+    and its step charge (FP64) or without: relative 1e-9 and, as for the
+    diagonal FP32 rollout, 1e-4."""
+    npd = np.float64 if dtype == F64 else np.float32
+    rng = np.random.default_rng(n + m)
+    prob = random_linear(n, m, T, p, 100 * n + m)
+    if "Q" in weights.replace("Qf", ""):
+        prob.Q = spd(n, rng)
+    if "R" in weights:
+        prob.R = 0.05 * spd(m, rng)
+    if "Qf" in weights:
+        prob.Qf = 2.0 * spd(n, rng)
+    if dtype == F64:
+        prob.x_min, prob.x_max = prob.x_goal - 0.3, prob.x_goal + 0.3
+        prob.qb, prob.sb = np.linspace(0.5, 2.0, n), np.linspace(0.1, 0.7, n)
+    prob = prob.cast(npd)
+    ld = ncand + 2
+    x0 = W.draw_x0(n, 4).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 6, ld=ld).astype(npd).astype(np.float64)
+    cost = dev(np.full(ncand + 4, np.nan), dtype)
+    E.empc_rollout_cost(E.DeviceProblem(prob, dtype), dev(x0, dtype), dev(knots, dtype), ncand, ld,
+                        cost)
+    got = cost.cpu().numpy()
+    assert np.isnan(got[ncand:]).all()  # nothing stored past the candidates
+    np.testing.assert_allclose(got[:ncand], oracle_lib.rollout_cost(prob, x0, knots, ncand),
+                               rtol=1e-9 if dtype == F64 else 1e-4)
