@@ -324,6 +324,22 @@ __device__ inline K wave_max(K v) {
     return v;
 }
 
+// Smallest key of the wavefront (uniform): row minima by DPP, then the four
+// rows' by lane reads; 64-bit keys by shuffles.  Every lane must be active.
+__device__ inline uint32_t key_min(uint32_t v) {
+    auto low = [](uint32_t a, int b) { return a < (uint32_t)b ? a : (uint32_t)b; };
+    v = low(v, __builtin_amdgcn_update_dpp(-1, (int)v, 0x111, 0xf, 0xf, false));
+    v = low(v, __builtin_amdgcn_update_dpp(-1, (int)v, 0x112, 0xf, 0xf, false));
+    v = low(v, __builtin_amdgcn_update_dpp(-1, (int)v, 0x114, 0xf, 0xf, false));
+    v = low(v, __builtin_amdgcn_update_dpp(-1, (int)v, 0x118, 0xf, 0xf, false));
+    const uint32_t a = low(__builtin_amdgcn_readlane((int)v, 15),
+                           __builtin_amdgcn_readlane((int)v, 31));
+    const uint32_t b = low(__builtin_amdgcn_readlane((int)v, 47),
+                           __builtin_amdgcn_readlane((int)v, 63));
+    return a < b ? a : b;
+}
+__device__ inline uint64_t key_min(uint64_t v) { return wave_min(v); }
+
 // Inverse of sort_key (NaN keys decode to a NaN, -0 to +0).
 __device__ inline float key_value(uint32_t k) {
     return __uint_as_float((k & 0x80000000u) ? (k & 0x7FFFFFFFu) : ~k);
@@ -333,6 +349,20 @@ __device__ inline double key_value(uint64_t k) {
         (long long)((k & 0x8000000000000000ull) ? (k & 0x7FFFFFFFFFFFFFFFull) : ~k));
 }
 
+// Before the radix passes there is a short cut: every wavefront takes the
+// r-th smallest of its threads' smallest keys (r = ceil(k / wavefronts), by
+// taking minima off one after another), and the largest of these over the
+// wavefronts is a threshold that at least k keys do not exceed, and usually
+// one and a half to three times k.  Those keys are compacted in index order
+// and ranked against each other by (key, index): ranks below k are the
+// parents.  If more keys than the workgroup has threads pass the threshold
+// (ties, k near the population), the radix passes follow.  Same total order,
+// same outputs.  Radix passes and short cut: one workgroup, 16384 costs 11.4
+// and 7.8 us; 512 workgroups of 256 threads and 1024 costs 41 and 37 us; but
+// 4096 costs in 1024 threads 6.3 and 7.2 us (four keys per thread make the
+// passes cheap, and the ranking is what is left), so that instance keeps the
+// passes alone.
+//
 // NREP: histogram replicas (a power of two <= 16); a one-wavefront selection
 // inside the persistent batched kernel takes 1 to keep its LDS small.
 template <typename T, typename K, int CACHE, int NTHR = SEL_THREADS, int NREP = HREP>
@@ -341,16 +371,23 @@ __device__ __forceinline__ void select_body(
     int pm, int m, int64_t *__restrict__ elite_idx_out, int64_t *__restrict__ best_idx_out,
     T *__restrict__ elite_rows, T *__restrict__ elite_cost, int *__restrict__ has_elites,
     int *__restrict__ best_slot_out, T *__restrict__ u_star, T *__restrict__ best_cost) {
-    __shared__ int hist[2][NREP * HSTRIDE];
+    __shared__ __align__(32) int hist[2][NREP * HSTRIDE];
     __shared__ int tot[256];
     __shared__ int wsum[(NTHR / 64)];
     __shared__ K s_lo[(NTHR / 64)], s_hi[(NTHR / 64)];
     __shared__ int64_t s_elite[Limits::MAX_ELITE];
     __shared__ K s_ekey[Limits::MAX_ELITE];
     __shared__ int s_best_slot;
+    // the short cut's candidates and ranks, in the histograms' memory
+    constexpr bool SHORT = CACHE > 0 && (NTHR == 256 || (NTHR > 256 && CACHE > 4));
+    static_assert(!SHORT || sizeof(hist) >= sizeof(K) * (NTHR + 64) + 8 * NTHR, "candidates fit");
+    K *s_ck = reinterpret_cast<K *>(&hist[0][0]);
+    int *s_ci = reinterpret_cast<int *>(s_ck + NTHR + 64), *s_rank = s_ci + NTHR;
+    __shared__ int wsum2[(NTHR / 64)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    for (int b = tid; b < NREP * HSTRIDE; b += NTHR) hist[0][b] = 0;
+    if constexpr (!SHORT)
+        for (int b = tid; b < NREP * HSTRIDE; b += NTHR) hist[0][b] = 0;
 
     const int64_t per = (pop + NTHR - 1) / NTHR;
     const int64_t i0 = (int64_t)tid * per;
@@ -385,6 +422,76 @@ __device__ __forceinline__ void select_body(
             for (int64_t r = 0; r < nmine; ++r) f(r, sort_key(cost[i0 + r]));
         }
     };
+    bool ranked = false;  // the short cut found the parents (uniform)
+    if constexpr (SHORT) {
+        constexpr int NW = NTHR / 64;
+        const int nact = (int)((pop + per - 1) / per);  // threads that hold a key
+        const int full = nact / 64;                     // wavefronts whose threads all do
+        const int r = full > 0 ? (k + full - 1) / full : 65;
+        if (r <= 64) {
+            K mn = ~(K)0;
+            for_each_key([&](int64_t, K key) { mn = key < mn ? key : mn; });
+            K tw = 0;
+            for (int taken = 0; taken < r;) {  // uniform; equal minima leave together
+                tw = key_min(mn);
+                const unsigned long long hit = __ballot(mn == tw);
+                taken += __popcll(hit);
+                if (mn == tw) mn = ~(K)0;
+            }
+            if (lane == 0) s_lo[wave] = wave < full ? tw : (K)0;
+            __syncthreads();
+            K thr = s_lo[0];
+#pragma unroll
+            for (int w = 1; w < NW; ++w) thr = s_lo[w] > thr ? s_lo[w] : thr;
+            int mine = 0, total;
+            for_each_key([&](int64_t, K key) { mine += key <= thr ? 1 : 0; });
+            int pos = block_excl_scan<NW>(mine, wsum, &total);
+            if (total <= NTHR) {  // uniform
+                for_each_key([&](int64_t q, K key) {
+                    if (key <= thr) {
+                        s_ck[pos] = key;
+                        s_ci[pos] = (int)(i0 + q);
+                        ++pos;
+                    }
+                });
+                if (tid < 64) s_ck[total + tid] = ~(K)0;  // whole groups of four below
+                __syncthreads();
+                // rank of candidate c, counted by L lanes, four keys at a time
+                int sh = 0;
+                while (sh < 4 && (total << (sh + 1)) <= NTHR) ++sh;
+                const int L = 1 << sh, c = tid >> sh;
+                int rank = 0;
+                if (c < total) {
+                    typedef K k4 __attribute__((ext_vector_type(4)));
+                    const K key = s_ck[c];
+#pragma unroll 2
+                    for (int j = 4 * (tid & (L - 1)); j < total; j += 4 * L) {
+                        const k4 o = *reinterpret_cast<const k4 *>(s_ck + j);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+                            rank += (o[q] < key || (o[q] == key && j + q < c)) ? 1 : 0;
+                    }
+                }
+                for (int q = 1; q < L; q <<= 1) rank += __shfl_xor(rank, q, 64);
+                if (c < total && (tid & (L - 1)) == 0) s_rank[c] = rank;
+                __syncthreads();
+                const bool in = tid < total && s_rank[tid] < k;
+                int kk;
+                const int slot = block_excl_scan<NW>(in ? 1 : 0, wsum2, &kk);
+                if (in) {
+                    s_elite[slot] = s_ci[tid];
+                    s_ekey[slot] = s_ck[tid];
+                    if (s_rank[tid] == 0) s_best_slot = slot;
+                }
+                ranked = true;
+            }
+        }
+    }
+    if (!ranked) {
+    if constexpr (SHORT) {
+        __syncthreads();  // s_lo is written again; the candidates' memory is free
+        for (int b = tid; b < NREP * HSTRIDE; b += NTHR) hist[0][b] = 0;
+    }
     {  // the block's smallest and largest key
         K lo = ~(K)0, hi = 0;
         for_each_key([&](int64_t, K key) {
@@ -511,6 +618,7 @@ __device__ __forceinline__ void select_body(
         }
         if (tid == 0) s_best_slot = bs < k ? bs : 0;
     }
+    }  // !ranked
     __syncthreads();
     const int bslot = s_best_slot;
     for (int s = tid; s < k; s += NTHR) {
@@ -518,6 +626,7 @@ __device__ __forceinline__ void select_body(
         if (elite_cost) elite_cost[s] = key_value(s_ekey[s]);
     }
     if (elite_rows)  // parameter-major: elite_rows[j k + s]
+#pragma unroll 4
         for (int t = tid; t < k * pm; t += NTHR) {
             const int j = t / k, s = t - j * k;
             elite_rows[t] = knots[(int64_t)j * ld + s_elite[s]];

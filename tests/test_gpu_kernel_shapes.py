@@ -221,3 +221,28 @@ def test_full_weights_shapes(oracle_lib, E, n, m, T, p, ncand, dtype, weights):
     assert np.isnan(got[ncand:]).all()  # nothing stored past the candidates
     np.testing.assert_allclose(got[:ncand], oracle_lib.rollout_cost(prob, x0, knots, ncand),
                                rtol=1e-9 if dtype == F64 else 1e-4)
+
+
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("pop,k", [(257, 256), (511, 40), (1000, 64), (1024, 32), (1024, 256),
+                                   (4097, 64), (6000, 1), (16384, 64), (16385, 200), (40000, 256)])
+def test_selection_short_cut_edges(oracle_lib, E, pop, k, dtype):
+    """Selection through the wavefronts' threshold and through the passes that
+    follow when it keeps too many costs: full and partly filled wavefronts,
+    the lowest costs spread, all in the first slots, all in the last ones, and
+    more equal costs at the threshold than a workgroup has threads.  Indices
+    are exact."""
+    from test_gpu_parity import gpu_generation
+
+    prob = W.linear_chain(2, 10, 3, seed=0)
+    ga = W.GA(pop=pop, n_elite=k, generations=1, sigma=0.1, seed=1)
+    rng = np.random.default_rng(pop + k)
+    spread = rng.normal(0, 1, pop).astype(np.float32).astype(np.float64)
+    equal = np.where(rng.random(pop) < 0.002, -1.0, 2.0)
+    knots = W.draw_knots(prob, pop, 1)
+    for cost in (spread, np.sort(spread), np.sort(spread)[::-1].copy(), equal,
+                 np.where(rng.random(pop) < 0.5, np.nan, spread)):
+        _, eidx, best = gpu_generation(E, prob, ga, knots, cost, 0, 0, dtype)
+        want_idx, want_best = oracle_lib.select(cost, k)
+        np.testing.assert_array_equal(eidx, want_idx)
+        assert best == want_best
