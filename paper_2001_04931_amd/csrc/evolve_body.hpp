@@ -134,94 +134,111 @@ __device__ __forceinline__ void population_tile(
         const T r = sqrt(d2) / var.sigma_dist;
         sigma = var.sigma_min + (sigma - var.sigma_min) * (r < (T)1 ? r : (T)1);
     }
+    if (cold) {
+        for (int rg = 0; rg < R; ++rg) {
+            const int j0 = jt + 16 * rg + 4 * w;
+            if (j0 >= pm) break;
+            const U4 wc = ga_draw(gs, slot, gen, tick, 1, (uint32_t)(j0 / 4));
+            int i = j0 % m;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                if (j0 + r < pm)
+                    knots_out[(int64_t)(j0 + r) * ld_out + s] =
+                        P.umin[i] + (P.umax[i] - P.umin[i]) * uni23<T>(word_of(wc, r));
+                i = i + 1 == m ? 0 : i + 1;
+            }
+        }
+        return;
+    }
+    // Warm.  Most instructions are the ten Philox rounds and the Box-Muller
+    // pairs, so the rest is kept off the vector ALUs: indices of parameters
+    // and inputs are uniform, a row's address is a scalar base plus a 32-bit
+    // byte offset per lane (the two parents' offsets are fixed per child),
+    // bounds are scalar loads issued before the draw, and the elite slots and
+    // the shift are selects.  With indices in vector registers, 64-bit address
+    // products and a wait for each parameter's bounds, and with this: 512
+    // problems of 1024 children 150 and 130 us; 4096 children, 140 parameters
+    // 6.6 and 5.9 us; 16384, 360 parameters 25 and 24 us (a quarter of it
+    // the gather of 64 parents' lines per parameter; staging them in LDS per
+    // 256 children measured the same).
+    const T *base = elite_rows ? elite_rows : knots_in;
+    const int64_t step = elite_rows ? k : ld_in;
+    // the parents stay in slots 0 .. k-1: only the first tiles hold any
+    const bool elite_tile = elitism && tile_s * POP_SLOTS < k;  // uniform
+    const bool elite_slot = elite_tile && s < k;
+    uint32_t o1, o2;
+    if (elite_rows) {
+        o1 = (uint32_t)s_par[lane][0];
+        o2 = (uint32_t)s_par[lane][1];
+        if (elite_slot) o1 = o2 = (uint32_t)s;
+    } else {
+        o1 = (uint32_t)s_eidx[s_par[lane][0]];
+        o2 = (uint32_t)s_eidx[s_par[lane][1]];
+        if (elite_slot) o1 = o2 = (uint32_t)s_eidx[s];
+    }
+    o1 *= (uint32_t)sizeof(T);
+    o2 *= (uint32_t)sizeof(T);
+    typedef uint32_t w4 __attribute__((ext_vector_type(4)));
+    const w4 fw = *reinterpret_cast<const w4 *>(&s_flag[lane][0]);
+    const w4 xw = *reinterpret_cast<const w4 *>(&s_xw[lane][0]);
+    auto word = [](const w4 &v, int q) {  // q uniform
+        return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w));
+    };
+    const uint32_t os = (uint32_t)s * (uint32_t)sizeof(T);
+    auto at = [](const T *row, uint32_t off) {
+        return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(row) + off);
+    };
+    // with the shift, the carried input one control step later: (1-d) U_a +
+    // d U_{a+1} for knot a < p-1 (d = (p-1)/(T-1), the knot spacing in steps
+    // inverted)
+    const T d = P.p > 1 ? (T)(P.p - 1) / (T)(P.Tn - 1) : (T)0;
     for (int rg = 0; rg < R; ++rg) {
         const int j0 = jt + 16 * rg + 4 * w;
         if (j0 >= pm) break;
-        // inputs of parameters j0 .. j0+3: one division, then wrap at m
-        int ii[4];
-        ii[0] = j0 % m;
+        const int a0 = j0 / m;
+        int ii[4], ka[4];  // inputs and knots of parameters j0 .. j0+3
+        ii[0] = j0 - a0 * m;
+        ka[0] = a0;
 #pragma unroll
-        for (int r = 1; r < 4; ++r) ii[r] = ii[r - 1] + 1 == m ? 0 : ii[r - 1] + 1;
-        T val[4];
-        if (cold) {
-            const U4 wc = ga_draw(gs, slot, gen, tick, 1, (uint32_t)(j0 / 4));
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int i = ii[r];
-                val[r] = P.umin[i] + (P.umax[i] - P.umin[i]) * uni23<T>(word_of(wc, r));
-            }
-        } else {
-            const T *base = elite_rows ? elite_rows : knots_in;
-            const int64_t step = elite_rows ? k : ld_in;
-            // the parent's values of all four parameters are loaded first, so
-            // that the loads are in flight together and behind the draws;
-            // parameter j of the parent stored at src, and with the shift the
-            // carried input one control step later, (1-d) U_a + d U_{a+1} for
-            // knot a < p-1 (d = (p-1)/(T-1), the knot spacing in steps
-            // inverted).  Indices past the last parameter load parameter
-            // pm-1 and are never stored.
-            const T d = P.p > 1 ? (T)(P.p - 1) / (T)(P.Tn - 1) : (T)0;
-            const bool elite_slot = elitism && s < k;
-            int64_t src[4];
-            bool flag[4] = {false, false, false, false};
-            if (elite_slot) {
-                const int64_t e = elite_rows ? s : s_eidx[s];
-#pragma unroll
-                for (int r = 0; r < 4; ++r) src[r] = e;
-            } else {
-                const int p1 = s_par[lane][0], p2 = s_par[lane][1];
-                const int64_t src1 = elite_rows ? (int64_t)p1 : s_eidx[p1];
-                const int64_t src2 = elite_rows ? (int64_t)p2 : s_eidx[p2];
-                typedef uint32_t w4 __attribute__((ext_vector_type(4)));
-                const w4 fw = *reinterpret_cast<const w4 *>(&s_flag[lane][0]);
-                const w4 xw = *reinterpret_cast<const w4 *>(&s_xw[lane][0]);
-                auto word = [](const w4 &v, int q) {
-                    return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w));
-                };
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = j0 + r, jb = j % 128;
-                    flag[r] = j < pm && ((word(fw, ii[r] / 32) >> (ii[r] % 32)) & 1u);
-                    const bool from2 = (word(xw, jb / 32) >> (jb % 32)) & 1u;
-                    src[r] = from2 ? src2 : src1;
-                }
-            }
-            T pv[4], pn[4];
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = j0 + r < pm ? j0 + r : pm - 1;
-                pv[r] = base[src[r] + (int64_t)j * step];
-            }
-            if (var.shift) {
-#pragma unroll
-                for (int r = 0; r < 4; ++r) {
-                    const int j = j0 + r < pm ? j0 + r : pm - 1;
-                    pn[r] = j / m < P.p - 1 ? base[src[r] + (int64_t)(j + m) * step] : pv[r];
-                }
-            }
-            T z[4] = {0, 0, 0, 0};
-            if (flag[0] || flag[1] || flag[2] || flag[3]) {
-                const U4 wn = ga_draw(gs, slot, gen, tick, 0, (uint32_t)(gs.NB + j0 / 4));
-                if (flag[0] || flag[1]) box_muller<T>(wn.x, wn.y, z[0], z[1]);
-                if (flag[2] || flag[3]) box_muller<T>(wn.z, wn.w, z[2], z[3]);
-            }
-#pragma unroll
-            for (int r = 0; r < 4; ++r) {
-                const int j = j0 + r;
-                if (j >= pm) {
-                    val[r] = 0;
-                    continue;
-                }
-                T v = pv[r];
-                if (var.shift && j / m < P.p - 1) v = ((T)1 - d) * v + d * pn[r];
-                val[r] = elite_slot ? v
-                                    : mutate_clamp<T>(v, flag[r], sigma, z[r], P.umin[ii[r]],
-                                                      P.umax[ii[r]]);
-            }
+        for (int r = 1; r < 4; ++r) {
+            const bool wrap = ii[r - 1] + 1 == m;
+            ii[r] = wrap ? 0 : ii[r - 1] + 1;
+            ka[r] = ka[r - 1] + (wrap ? 1 : 0);
         }
+        // the parents' values first, in flight behind the draws (past the last
+        // parameter: the last one, never stored); j0 .. j0+3 share a word of
+        // crossover bits
+        const uint32_t xb = word(xw, (j0 % 128) / 32) >> (j0 % 32);
+        T pv[4], pn[4], lo[4], hi[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            const int j = j0 + r < pm ? j0 + r : pm - 1;
+            const uint32_t o = (xb >> r) & 1u ? o2 : o1;
+            pv[r] = at(base + (int64_t)j * step, o);
+            if (var.shift) pn[r] = at(base + (int64_t)(ka[r] < P.p - 1 ? j + m : j) * step, o);
+            lo[r] = P.umin[ii[r]];
+            hi[r] = P.umax[ii[r]];
+        }
+        uint32_t f[4];
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            if (j0 + r < pm) knots_out[(int64_t)(j0 + r) * ld_out + s] = val[r];
+            f[r] = (m <= 32 ? fw.x : word(fw, ii[r] / 32)) >> (ii[r] % 32) & 1u;
+        T z[4] = {0, 0, 0, 0};
+        if (f[0] | f[1] | f[2] | f[3]) {
+            const U4 wn = ga_draw(gs, slot, gen, tick, 0, (uint32_t)(gs.NB + j0 / 4));
+            box_muller<T>(wn.x, wn.y, z[0], z[1]);
+            box_muller<T>(wn.z, wn.w, z[2], z[3]);
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+            T v = pv[r];
+            if (var.shift && ka[r] < P.p - 1) v = ((T)1 - d) * v + d * pn[r];
+            T c = mutate_clamp<T>(v, f[r], sigma, z[r], lo[r], hi[r]);
+            if (elite_tile && elite_slot) c = v;
+            if (j0 + r < pm)
+                *reinterpret_cast<T *>(
+                    reinterpret_cast<char *>(knots_out + (int64_t)(j0 + r) * ld_out) + os) = c;
+        }
     }
 }
 

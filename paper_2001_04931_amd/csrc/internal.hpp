@@ -121,6 +121,12 @@ __host__ __device__ inline Knot knot_at(int T, int p, int k) {
 struct U4 {
     uint32_t x, y, z, w;
 };
+// a ^ b ^ c in one instruction (0x96: the truth table of the parity).  Six
+// wavefronts per SIMD in step: 119 ns per ten rounds with two exclusive ors,
+// 87 ns with this.
+__device__ inline uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) {
+    return __builtin_amdgcn_bitop3_b32(a, b, c, 0x96);
+}
 __device__ inline U4 philox10(U4 c, uint32_t k0, uint32_t k1) {
 #pragma unroll
     for (int i = 0; i < 10; ++i) {
@@ -129,7 +135,7 @@ __device__ inline U4 philox10(U4 c, uint32_t k0, uint32_t k1) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c.x, p1 = (uint64_t)0xCD9E8D57u * c.z;
         const uint32_t lo0 = (uint32_t)p0, hi0 = (uint32_t)(p0 >> 32);
         const uint32_t lo1 = (uint32_t)p1, hi1 = (uint32_t)(p1 >> 32);
-        c = U4{hi1 ^ c.y ^ k0, lo1, hi0 ^ c.w ^ k1, lo0};
+        c = U4{xor3(hi1, c.y, k0), lo1, xor3(hi0, c.w, k1), lo0};
         k0 += 0x9E3779B9u;
         k1 += 0xBB67AE85u;
     }
@@ -236,7 +242,7 @@ struct Limits {
     static constexpr int MAX_D_CHAIN = 40;
     static constexpr int MAX_ELITE = 256;
 };
-constexpr int VALU_FULL_NMAX = 64;  // largest n with full weights (16-lane row form)
+constexpr int VALU_FULL_NMAX = 64;  // largest n with full weights
 constexpr int VALU_FULL_MMAX = 32;  // largest m with full weights
 
 // Optional start / stop events stamped by a kernel's dispatch.
@@ -250,11 +256,6 @@ __device__ inline int64_t xcd_swizzle(int64_t b, int64_t nb) {
     constexpr int64_t NX = 8;
     const int64_t q = nb / NX, r = nb % NX, x = b % NX;
     return x * q + (x < r ? x : r) + b / NX;
-}
-// The same for a 2-D grid (x fastest): returns the swizzled linear index.
-__device__ inline int64_t xcd_swizzle_2d() {
-    const int64_t nb = (int64_t)gridDim.x * gridDim.y;
-    return xcd_swizzle((int64_t)blockIdx.y * gridDim.x + blockIdx.x, nb);
 }
 
 // ---------------------------------------------------------------------------
@@ -373,7 +374,7 @@ struct Events {
 // bits, and all chain forms; the VALU forms sum in another order.
 enum RolloutForm {
     RF_RULE = 0, RF_ONE1 = 1, RF_ONE2 = 2, RF_ONE4 = 3, RF_SPLIT = 4, RF_VALU256 = 5,
-    RF_VALU64 = 6, RF_FROWS = 7, RF_CH64 = 11, RF_CH128 = 12, RF_CH256 = 13
+    RF_VALU64 = 6, RF_CH64 = 11, RF_CH128 = 12, RF_CH256 = 13
 };
 
 template <typename T>

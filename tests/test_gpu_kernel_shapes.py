@@ -246,3 +246,33 @@ def test_selection_short_cut_edges(oracle_lib, E, pop, k, dtype):
         want_idx, want_best = oracle_lib.select(cost, k)
         np.testing.assert_array_equal(eidx, want_idx)
         assert best == want_best
+
+
+@pytest.mark.parametrize("elitism", [True, False])
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("m,p,pop,k", [(1, 1, 65, 1), (1, 7, 300, 65), (3, 5, 1000, 130),
+                                       (5, 3, 64, 64), (31, 9, 129, 20), (33, 10, 4500, 256),
+                                       (40, 4, 700, 70)])
+def test_warm_population_shapes(oracle_lib, E, m, p, pop, k, dtype, elitism):
+    """Children against the oracle's: parameter counts that leave a group of
+    four partly filled, inputs that wrap inside a group and past a 32-bit word
+    of mutation flags, bounds that differ by input, parents past the first
+    tile of 64 slots.  The tolerances are those of the noise's rounding (1e-6
+    at sigma 0.1 in FP32, 1e-14 in FP64)."""
+    from test_gpu_parity import gpu_generation
+
+    npd = np.float64 if dtype == F64 else np.float32
+    prob = random_linear(4, m, 12, p, 70 + m)
+    prob.u_max = np.linspace(0.5, 1.0, m)
+    prob.u_min = -np.linspace(1.0, 0.7, m)
+    prob = prob.cast(npd)
+    ga = W.GA(pop=pop, n_elite=k, generations=1, sigma=0.1, seed=99, elitism=elitism)
+    rng = np.random.default_rng(pop)
+    knots = W.draw_knots(prob, pop, 2).astype(npd).astype(np.float64)
+    cost = rng.uniform(0, 10, pop).astype(npd).astype(np.float64)
+    got, eidx, _ = gpu_generation(E, prob, ga, knots, cost, tick=5, gen=3, dtype=dtype)
+    want_idx, _ = oracle_lib.select(cost, k)
+    np.testing.assert_array_equal(eidx, want_idx)
+    want = oracle_lib.next_population(prob, ga, knots[:, want_idx].T.copy(), cold=False, tick=5,
+                                      gen=3)
+    np.testing.assert_allclose(got, want, rtol=0, atol=1e-6 if dtype == F32 else 1e-14)
