@@ -276,3 +276,30 @@ def test_warm_population_shapes(oracle_lib, E, m, p, pop, k, dtype, elitism):
     want = oracle_lib.next_population(prob, ga, knots[:, want_idx].T.copy(), cold=False, tick=5,
                                       gen=3)
     np.testing.assert_allclose(got, want, rtol=0, atol=1e-6 if dtype == F32 else 1e-14)
+
+
+@pytest.mark.parametrize("option", ["plain", "goal", "box"])
+@pytest.mark.parametrize("dtype", [F32, F64])
+@pytest.mark.parametrize("n,m,T,p,ncand", [(1, 1, 1, 1, 1), (3, 2, 9, 4, 17), (4, 4, 20, 20, 64),
+                                           (4, 8, 13, 1, 130), (5, 5, 12, 3, 16), (8, 1, 30, 6, 90),
+                                           (8, 8, 21, 5, 15), (9, 4, 10, 2, 33)])
+def test_few_states_rollout(oracle_lib, E, n, m, T, p, ncand, dtype, option):
+    """Linear rollouts at both ends of the compile-time slice counts (up to 4,
+    up to 8, more states), against the FP64 oracle: relative 1e-9 and 1e-4."""
+    npd = np.float64 if dtype == F64 else np.float32
+    prob = random_linear(n, m, T, p, 30 * n + m)
+    if option == "plain":
+        prob.x_goal = None
+    if option == "box":
+        prob.x_min, prob.x_max = prob.x_goal - 0.3, prob.x_goal + 0.3
+        prob.qb = np.linspace(0.5, 2.0, n)
+    prob = prob.cast(npd)
+    x0 = W.draw_x0(n, 8).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 9, ld=ncand + 1).astype(npd).astype(np.float64)
+    cost = dev(np.full(ncand + 3, np.nan), dtype)
+    E.empc_rollout_cost(E.DeviceProblem(prob, dtype), dev(x0, dtype), dev(knots, dtype), ncand,
+                        ncand + 1, cost)
+    got = cost.cpu().numpy()
+    assert np.isnan(got[ncand:]).all()
+    np.testing.assert_allclose(got[:ncand], oracle_lib.rollout_cost(prob, x0, knots, ncand),
+                               rtol=1e-9 if dtype == F64 else 1e-4)
