@@ -146,23 +146,26 @@ def _ptr(t: Optional[torch.Tensor]):
         return None
     if not t.is_cuda:
         raise ValueError("expected a GPU tensor")
-    return ctypes.c_void_p(t.data_ptr())
+    return t.data_ptr()
 
 
 def _stream(stream=None):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    # the handle itself, without a Stream object around it: the calls below
+    # take argument types, so plain integers become pointers there
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
 
 
 def _cprob(prob):
-    return ctypes.byref(prob.c if hasattr(prob, "c") else prob)
+    return ctypes.byref(getattr(prob, "c", prob))
 
 
 def _shape(prob):
     """(torch dtype, n, m, p*m) of a DeviceProblem or a bare EmpcProblem."""
-    c = prob.c if hasattr(prob, "c") else prob
-    dt = torch.float64 if c.dtype == EMPC_F64 else torch.float32
-    return dt, int(c.n), int(c.m), int(c.p) * int(c.m)
+    c = getattr(prob, "c", prob)
+    m = c.m
+    return torch.float64 if c.dtype == EMPC_F64 else torch.float32, c.n, m, c.p * m
 
 
 def _need(t, dtype, numel, name, optional=False):
@@ -500,7 +503,7 @@ class EmpcCost(torch.autograd.Function):
     @staticmethod
     def backward(ctx, grad_cost):
         (dJ,) = ctx.saved_tensors
-        return dJ * grad_cost.unsqueeze(0), None, None
+        return dJ * grad_cost, None, None
 
 
 class BatchSolver:
