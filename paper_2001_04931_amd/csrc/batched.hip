@@ -22,7 +22,7 @@ namespace empc {
 // One workgroup per (problem, population tile) that holds parameters: the
 // map lists them problem after problem, so problems with fewer parameters
 // take fewer workgroups (no workgroups that would only exit).
-template <typename T>
+template <typename T, typename OFF>
 __global__ __launch_bounds__(POP_THREADS) void batch_population(const BatchSlot<T> *__restrict__ slots,
                                                         const int2 *__restrict__ popmap,
                                                         int64_t pop, int k, int elitism, T sigma,
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(POP_THREADS) void batch_population(const BatchSlot<
     var.sigma_min = sigma_min;
     var.sigma_dist = sigma_dist;
     var.shift = first ? shift : 0;
-    population_tile<T>(P, gs, pop, k, elitism, sigma,
+    population_tile<T, OFF>(P, gs, pop, k, elitism, sigma,
                        first ? nullptr : global_ptr(S.knots[(g + 1) & 1]), pop,
                        first ? nullptr : global_ptr(S.elite_idx),
                        first ? global_ptr(S.elite_rows) : nullptr, cold,
@@ -537,6 +537,22 @@ void assign_streams(empc_batch *b, int ns) {
     }
 }
 
+// population of generation g, all problems (counters: see batch_population)
+void launch_batch_population(empc_batch *b, int g, unsigned *counters, int ncounters,
+                             hipStream_t s) {
+    const empc_ga &G = b->ga;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)b->pop_wgs), dim3(POP_THREADS), 0, s, b->d_slots,
+                           b->d_popmap, b->pop, G.n_elite, G.elitism, (float)G.sigma,
+                           (uint32_t)G.seed, g, (const uint32_t *)b->d_tick, G.shift,
+                           (float)G.sigma_min, (float)G.sigma_dist, b->pop_r, counters, ncounters);
+    };
+    if (b->pop <= POP_NARROW<float>)
+        go(batch_population<float, uint32_t>);
+    else
+        go(batch_population<float, uint64_t>);
+}
+
 // The rollouts of one generation: fork the side streams from s, each class
 // on its stream, join them back into s.
 hipError_t rollout_phase(empc_batch *b, int g, hipStream_t s) {
@@ -863,27 +879,18 @@ empc_status empc_solve_batched(empc_batch *b, void *stream) {
     if (!b) return empc_fail_internal(EMPC_EINVAL, "batch is NULL");
     hipStream_t s = (hipStream_t)stream;
     const empc_ga &G = b->ga;
-    const int64_t pop = b->pop;
-    const uint32_t seed_lo = (uint32_t)G.seed;
     if (b->mode == 1) {
         const int ncounters = PTIERS + 1 + b->nprob;
         for (int g = 0; g < G.generations; ++g) {
             const int last = g == G.generations - 1;
-            hipLaunchKernelGGL(batch_population<float>, dim3((unsigned)b->pop_wgs),
-                               dim3(POP_THREADS), 0, s, b->d_slots, b->d_popmap, pop, G.n_elite,
-                               G.elitism, (float)G.sigma, seed_lo, g, (const uint32_t *)b->d_tick,
-                               G.shift, (float)G.sigma_min, (float)G.sigma_dist, b->pop_r,
-                               b->d_counters, ncounters);
+            launch_batch_population(b, g, b->d_counters, ncounters, s);
             const hipError_t fe = persist_phase(b, g, last, s);
             if (fe != hipSuccess) return empc_fail_internal(EMPC_EDEVICE, hipGetErrorString(fe));
         }
         return EMPC_OK;
     }
     for (int g = 0; g < G.generations; ++g) {
-        hipLaunchKernelGGL(batch_population<float>, dim3((unsigned)b->pop_wgs), dim3(POP_THREADS), 0,
-                           s, b->d_slots, b->d_popmap, pop, G.n_elite, G.elitism, (float)G.sigma,
-                           seed_lo, g, (const uint32_t *)b->d_tick, G.shift, (float)G.sigma_min,
-                           (float)G.sigma_dist, b->pop_r, (unsigned *)nullptr, 0);
+        launch_batch_population(b, g, nullptr, 0, s);
         const hipError_t fe = rollout_phase(b, g, s);
         if (fe != hipSuccess) return empc_fail_internal(EMPC_EDEVICE, hipGetErrorString(fe));
         launch_batch_select(b, nullptr, b->nprob, g, g == G.generations - 1, s);
@@ -898,14 +905,10 @@ empc_status empc_batch_autotune(empc_batch *b, int32_t reps, void *stream) {
     if (!b) return empc_fail_internal(EMPC_EINVAL, "batch is NULL");
     if (reps < 1) return empc_fail_internal(EMPC_EINVAL, "reps must be >= 1");
     hipStream_t s = (hipStream_t)stream;
-    const empc_ga &G = b->ga;
     // a generation-0 population, so that the timed rollouts read defined
     // knots; the parents, costs kept across ticks and the tick counter are
     // left as they are
-    hipLaunchKernelGGL(batch_population<float>, dim3((unsigned)b->pop_wgs), dim3(POP_THREADS), 0, s,
-                       b->d_slots, b->d_popmap, b->pop, G.n_elite, G.elitism,
-                       (float)G.sigma, (uint32_t)G.seed, 0, (const uint32_t *)b->d_tick, G.shift,
-                       (float)G.sigma_min, (float)G.sigma_dist, b->pop_r, (unsigned *)nullptr, 0);
+    launch_batch_population(b, 0, nullptr, 0, s);
     hipEvent_t t0 = nullptr, t1 = nullptr;
     hipError_t e = hipGetLastError();
     if (e == hipSuccess) e = hipEventCreate(&t0);
