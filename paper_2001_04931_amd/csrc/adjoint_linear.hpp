@@ -384,8 +384,11 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
             T *at = slot(0);
             XT = march(
                 0, Tn, X0, at,
-                [&](int k) -> T * {  // x_T is not read back: it goes where x_0 was
-                    at = k < Tn ? at + NT * 256 : slot(0);
+                // x_T is not read back: it goes into the ring of lambda, which is
+                // idle here (not into a state's slot: other wavefronts may still
+                // be reading the last step's, which for T = 1 is x_0's)
+                [&](int k) -> T * {
+                    at = k < Tn ? at + NT * 256 : sm + G.oL;
                     return at;
                 },
                 add);

@@ -1,0 +1,85 @@
+"""Linear gradients and refinement on the matrix cores against the FP64 oracle.
+
+Which kernel a call takes depends on the state count, the dtype and the number
+of candidates; the counts here are chosen for the matrix-core kernel unless a
+test says otherwise."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from test_gpu_kernel_shapes import F32, F64, dev, random_linear
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    import paper_2001_04931_amd as E
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    E.lib()
+    return E
+
+
+def case(n, m, T, p, ncand, dtype, box=False, seed=0, x0_scale=0.5):
+    """(problem, x0, knots [p m][ncand + 3]) rounded to the dtype."""
+    npd = np.float64 if dtype == F64 else np.float32
+    prob = random_linear(n, m, T, p, 10 * n + m + seed)
+    if box:
+        prob.x_min, prob.x_max = prob.x_goal - 0.3, prob.x_goal + 0.3
+        prob.qb, prob.sb = np.linspace(0.5, 2.0, n), np.linspace(0.1, 0.7, n)
+    prob = prob.cast(npd)
+    x0 = W.draw_x0(n, 3, scale=x0_scale).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 5, ld=ncand + 3).astype(npd).astype(np.float64)
+    return prob, x0, knots
+
+
+def check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype, step_charge=False):
+    """FP64: 1e-9 of a column's largest entry (gradient), 1e-10 (cost); FP32:
+    2e-3 and 1e-4, the rounding of T dependent steps."""
+    dp, K = E.DeviceProblem(prob, dtype), dev(knots, dtype)
+    dJ, cost = torch.full_like(K, float("nan")), dev(np.full(ncand + 2, np.nan), dtype)
+    E.empc_grad(dp, dev(x0, dtype), K, ncand, knots.shape[1], dJ, cost)
+    want, wcost = oracle_lib.grad(prob, x0, knots, ncand)
+    got, gcost = dJ.cpu().numpy().astype(np.float64), cost.cpu().numpy().astype(np.float64)
+    assert np.isnan(got[:, ncand:]).all() and np.isnan(gcost[ncand:]).all()
+    err = np.abs(got[:, :ncand] - want[:, :ncand]).max(axis=0)
+    scale = np.abs(want[:, :ncand]).max(axis=0)
+    tg, tc = (1e-9, 1e-10) if dtype == F64 else (2e-3, 1e-4)
+    assert (err <= tg * scale + 1e-30).all()
+    np.testing.assert_allclose(gcost[:ncand], wcost, rtol=tc)
+    return gcost[:ncand]
+
+
+def check_refine(oracle_lib, E, prob, x0, knots, ncand, dtype, steps=3):
+    """Adam steps of 0.01.  FP64: the oracle's knots and costs to 1e-9.  FP32:
+    the sign of a gradient component near zero moves a knot by a whole step, so
+    the knots are held against their own cost: the reported cost is the
+    oracle's cost of the refined knots (1e-4) and lies below the entry cost."""
+    K = dev(knots, dtype)
+    entry = oracle_lib.rollout_cost(prob, x0, knots, ncand)
+    C = dev(entry, dtype)
+    E.empc_refine(E.DeviceProblem(prob, dtype), dev(x0, dtype), K, ncand, knots.shape[1], C, 0.01,
+                  steps)
+    got, gc = K.cpu().numpy().astype(np.float64), C.cpu().numpy().astype(np.float64)
+    np.testing.assert_array_equal(got[:, ncand:], knots[:, ncand:])
+    if dtype == F64:
+        wk, wc = oracle_lib.refine(prob, x0, knots[:, :ncand].copy(), entry, lr=0.01, steps=steps)
+        np.testing.assert_allclose(gc, wc, rtol=1e-9)
+        np.testing.assert_allclose(got[:, :ncand], wk, rtol=0, atol=1e-9)
+    else:
+        np.testing.assert_allclose(gc, oracle_lib.rollout_cost(prob, x0, got, ncand), rtol=1e-4)
+        moved = np.any(got[:, :ncand] != knots[:, :ncand], axis=0)
+        assert moved.mean() > 0.5 and (gc[moved] <= entry[moved] * (1 + 1e-4)).all()
+
+
+@pytest.mark.parametrize("n,m,ncand,dtype", [(17, 4, 20, F32), (33, 9, 40, F32), (48, 33, 16, F32),
+                                             (49, 17, 530, F32), (17, 17, 530, F64),
+                                             (33, 5, 515, F64)])
+def test_one_step_horizon(oracle_lib, E, n, m, ncand, dtype):
+    """T = 1 with several wavefronts per tile: the only step reads the other
+    wavefronts' rows of x_0, which nothing may overwrite in the meantime."""
+    prob, x0, knots = case(n, m, 1, 1, ncand, dtype)
+    check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype)
+    check_refine(oracle_lib, E, prob, x0, knots, ncand, dtype)
