@@ -156,6 +156,10 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
     r_times(Ka, REa);
     r_times(Kb, REb);
     const T inv_den = Tn > 1 ? (T)1 / (T)(Tn - 1) : (T)0;
+    // Stage costs summed per state row: one running sum over a lane's four rows
+    // rounds four times as often (FP32, n = 14, 400 steps: rms relative error
+    // 2.2e-7 that way, 1.0e-7 per row), for 2 to 4 % of the time
+    v4 Js = {0, 0, 0, 0};
     T J = 0;
     int buf = 0, k = 0;
     for (int a = 0; a < p; ++a) {
@@ -178,10 +182,9 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
             if (NT > 1) xs[buf][w][lane] = X;
             // stage cost of x_k (x_0 has none), beside the new state's way
             const v4 QE = contract(aQ, V, -Qg);
-            T t = 0;
 #pragma unroll
-            for (int v = 0; v < 4; ++v) t += (Xk[v] - Xg[v]) * QE[v];
-            J = k > 0 ? J + t : (T)0;
+            for (int v = 0; v < LV; ++v)
+                Js[v] = k > 0 ? Js[v] + (Xk[v] - Xg[v]) * QE[v] : (T)0;
             if (BOX) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {  // x_{k+1}'s
@@ -241,7 +244,7 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        J += (X[v] - Xg[v]) * (QE[v] + F[v]);
+        J += Js[v] + (X[v] - Xg[v]) * (QE[v] + F[v]);
         if (BOX) {
             const int row = 16 * w + Mfma<T>::row(grp, v);
             const bool in = row < n;

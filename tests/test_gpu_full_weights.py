@@ -1,0 +1,52 @@
+"""FP32 costs with full weights: how exact they are (shapes and options are
+covered elsewhere)."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from test_gpu_kernel_shapes import F32, dev
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def E():
+    import paper_2001_04931_amd as E
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    E.lib()
+    return E
+
+
+def cost_error(oracle_lib, E, prob, x0, knots, ncand):
+    """Relative errors of the FP32 costs against the FP64 oracle's."""
+    cost = dev(np.full(ncand, np.nan), F32)
+    E.empc_rollout_cost(E.DeviceProblem(prob, F32), dev(x0, F32), dev(knots, F32), ncand, ncand,
+                        cost)
+    want = oracle_lib.rollout_cost(prob, x0, knots, ncand)
+    return cost.cpu().numpy().astype(np.float64) / want - 1.0
+
+
+@pytest.mark.parametrize("n,m", [(14, 7), (16, 8)])
+def test_stage_costs_are_summed_per_state_row(oracle_lib, E, n, m):
+    """400 steps, a knot every other one, |A| = 0.5: the states stay equally large
+    and their own rounding does not build up (below 0.5e-7 of the cost).  A
+    running sum of N equal positive terms has a relative error of u sqrt(N / 3)
+    rms (u = 2^-24 / sqrt(3), the rms rounding of an addition): summed per row
+    (N = T), n rows averaging, 1.1e-7; over the four rows of a lane (N = 4 T),
+    four lanes averaging, up to 3.9e-7.  The bound is sqrt(1.1^2 + 0.5^2) with a
+    quarter to spare."""
+    T, p, ncand = 400, 200, 512
+    rng = np.random.default_rng(n)
+    A = rng.normal(0, 1, (n, n))
+    A *= 0.5 / np.linalg.norm(A, 2)
+    off = rng.uniform(-0.02, 0.02, (n, n))
+    prob = W.Problem(model=W.LINEAR, n=n, m=m, T=T, p=p, Ad=A, Bd=rng.normal(0, 0.3, (n, m)),
+                     q=np.ones(n), r=np.full(m, 0.01), qf=np.zeros(n), x_goal=np.zeros(n),
+                     u_goal=np.zeros(m), u_min=-np.ones(m), u_max=np.ones(m),
+                     Q=np.eye(n) + off + off.T).cast(np.float32)
+    x0 = W.draw_x0(n, 4, scale=1.0).astype(np.float32).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 3).astype(np.float32).astype(np.float64)
+    err = cost_error(oracle_lib, E, prob, x0, knots, ncand)
+    assert np.sqrt(np.mean(err**2)) < 1.5e-7
