@@ -7,7 +7,7 @@
 // contraction over the same B operands as A_d x_k: its 4 NT MFMAs per step
 // depend on nothing in the step, so they run while the new state's sums
 // finish and go through LDS.  The stage cost adds (x - g)^T (Q x - Q g) with
-// Q g precomputed.  The input cost of a knot segment is closed form in
+// Q g precomputed (at x_T, Q (x - g)).  The input cost of a knot segment is closed form in
 // E_a = U_a - u_g and R E_a, one product per knot:
 //   S00 E_a^T R E_a + 2 S01 E_a^T R E_b + S11 E_b^T R E_b
 // with the sums of (1-c)^2, c (1-c), c^2 over the segment.  The terminal
@@ -214,12 +214,22 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
             r_times(Kb, REb);
         }
     }
-    // x_T: stage and terminal weight
-    gather(buf, V);
-    const v4 QE = contract(aQ, V, -Qg);
+    // x_T: stage and terminal weight of E = x_T - g, published like a state (not
+    // Q x - Q g: at a state near a goal far from the origin, where x_T is meant
+    // to be, the two cancel)
+    const v4 E = X - Xg;
+    {
+        const v4 x = X;
+        X = E;
+        // over this wavefront's tile of x_T, which no other has read (the other
+        // buffer is the one that they may still be reading)
+        if (NT > 1) xs[buf][w][lane] = X;
+        gather(buf, V);
+        X = x;
+    }
+    const v4 QE = contract(aQ, V, v4{0, 0, 0, 0});
     v4 F = {0, 0, 0, 0};
     if (P.Qfm) {
-        // (x - g) of every tile, published like a state
         T aF[4 * NT];
 #pragma unroll
         for (int i = 0; i < NT; ++i)
@@ -228,23 +238,17 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
                 const int kk = 16 * ((w + i) % NT) + Mfma<T>::row(grp, v);
                 aF[4 * i + v] = arow < n && kk < n ? P.Qfm[arow * n + kk] : (T)0;
             }
-        const v4 x = X;
-        X = X - Xg;
-        buf ^= 1;
-        if (NT > 1) xs[buf][w][lane] = X;
-        gather(buf, V);
         F = contract(aF, V, v4{0, 0, 0, 0});
-        X = x;
     } else if (P.qf) {
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * w + Mfma<T>::row(grp, v);
-            F[v] = row < n ? P.qf[row] * (X[v] - Xg[v]) : (T)0;
+            F[v] = row < n ? P.qf[row] * E[v] : (T)0;
         }
     }
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
-        J += Js[v] + (X[v] - Xg[v]) * (QE[v] + F[v]);
+        J += Js[v] + E[v] * (QE[v] + F[v]);
         if (BOX) {
             const int row = 16 * w + Mfma<T>::row(grp, v);
             const bool in = row < n;

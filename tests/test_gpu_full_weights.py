@@ -5,7 +5,7 @@ import pytest
 import torch
 
 import workloads as W
-from test_gpu_kernel_shapes import F32, dev
+from test_gpu_kernel_shapes import F32, dev, spd
 
 pytestmark = pytest.mark.gpu
 
@@ -50,3 +50,23 @@ def test_stage_costs_are_summed_per_state_row(oracle_lib, E, n, m):
     knots = W.draw_knots(prob, ncand, 3).astype(np.float32).astype(np.float64)
     err = cost_error(oracle_lib, E, prob, x0, knots, ncand)
     assert np.sqrt(np.mean(err**2)) < 1.5e-7
+
+
+@pytest.mark.parametrize("n", [3, 7, 16, 20, 40, 64])
+def test_terminal_cost_near_a_distant_goal(oracle_lib, E, n):
+    """One step that leaves the state where it is, one to three units from a goal
+    4096 away from the origin, both held exactly by FP32.  The cost of x_T - g
+    is a sum of n^2 terms, each rounded a few times: n + 4 units in the last
+    place of the sum of their sizes at most.  Q x_T - Q g would be off by about
+    4096 units in the last place of Q."""
+    rng = np.random.default_rng(n)
+    Q = spd(n, rng)
+    g = rng.choice([-4096.0, 4096.0], n)
+    prob = W.Problem(model=W.LINEAR, n=n, m=1, T=1, p=1, Ad=np.eye(n), Bd=np.zeros((n, 1)),
+                     q=np.ones(n), r=np.ones(1), qf=np.zeros(n), x_goal=g, u_goal=np.zeros(1),
+                     u_min=-np.ones(1), u_max=np.ones(1), Q=Q, Qf=0.3 * Q).cast(np.float32)
+    x0 = g + rng.integers(1, 4, n)
+    e = x0 - g
+    size = np.abs(e) @ np.abs(prob.Q + prob.Qf) @ np.abs(e) / (e @ (prob.Q + prob.Qf) @ e)
+    err = cost_error(oracle_lib, E, prob, x0, np.zeros((1, 20)), 20)
+    assert np.abs(err).max() <= (n + 4) * 2.0**-24 * size
