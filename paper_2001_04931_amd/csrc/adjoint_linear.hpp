@@ -233,8 +233,8 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
         return V[0] + V[1];
     };
     // states x_{k0+1} .. x_{k1} from X = x_{k0}, which every wavefront has
-    // stored at `at`; to(k): where x_k goes; each(X): called in the shadow of
-    // the step that leaves X
+    // stored at `at`; to(k): where x_k goes; each(x_k, k): called in the shadow
+    // of the step that leaves x_k
     auto march = [&](int k0, int k1, v4 X, T *at, auto &&to, auto &&each)
                      __attribute__((always_inline)) {
         int a = p == 1 || Tn == 1 ? 0 : k0 * (p - 1) / (Tn - 1);
@@ -246,7 +246,7 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
             for (; k < ke; ++k) {
                 const v4 s0 = start;
                 X = contract(aX, X, at, s0, [&, X]() {
-                    each(X);
+                    each(X, k);
                     start = Va + weight(k + 1, a) * dV;
                 });
                 at = to(k + 1);
@@ -355,27 +355,21 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
     // cost of the knots in sU; leaves the states in LDS and x_T in XT
     v4 XT = X0;
     auto forward = [&]() __attribute__((always_inline)) -> T {
-        // sums over x_1 .. x_T: every step adds the state that it leaves (x_0's
-        // terms cancel exactly against the start values), x_T follows
-        v4 S, Pn, Cn;
-#pragma unroll
-        for (int v = 0; v < 4; ++v) {
-            const T e = X0[v] - Xg[v];
-            S[v] = -(e * e);
-            Pn[v] = box ? -box_pen(X0[v], Lo[v], Hi[v]) : (T)0;
-            Cn[v] = box ? -box_out(X0[v], Lo[v], Hi[v]) : (T)0;
-        }
-        auto add = [&](const v4 &X) {
+        // sums over x_1 .. x_T: every step adds the state that it leaves, x_T
+        // follows; x_0's terms are left out (selects: a branch would cut the
+        // step), not subtracted, as their rounding would stay in the sums
+        v4 S = {0, 0, 0, 0}, Pn = {0, 0, 0, 0}, Cn = {0, 0, 0, 0};
+        auto add = [&](const v4 &X, int k) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
                 const T e = X[v] - Xg[v];
-                S[v] += e * e;
+                S[v] = k > 0 ? S[v] + e * e : (T)0;
             }
             if (box) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {
-                    Pn[v] += box_pen(X[v], Lo[v], Hi[v]);
-                    Cn[v] += box_out(X[v], Lo[v], Hi[v]);
+                    Pn[v] = k > 0 ? Pn[v] + box_pen(X[v], Lo[v], Hi[v]) : (T)0;
+                    Cn[v] = k > 0 ? Cn[v] + box_out(X[v], Lo[v], Hi[v]) : (T)0;
                 }
             }
         };
@@ -407,7 +401,7 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
                 },
                 add);
         }
-        add(XT);
+        add(XT, Tn);
         T J = 0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
@@ -452,7 +446,7 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
                 *tile(seg, w) = X;
                 march(k0, k1 - 1, X, slot(blk),
                       [&](int k) -> T * { return seg + (k - k0) * (NT * 256); },
-                      [](const v4 &) {});
+                      [](const v4 &, int) {});
             }
             v4 X = *tile(seg + (k1 - 1 - k0) * (NT * 256), w);
             for (int k = k1 - 1; k >= k0; --k) {

@@ -83,3 +83,30 @@ def test_one_step_horizon(oracle_lib, E, n, m, ncand, dtype):
     prob, x0, knots = case(n, m, 1, 1, ncand, dtype)
     check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype)
     check_refine(oracle_lib, E, prob, x0, knots, ncand, dtype)
+
+
+@pytest.mark.parametrize("dtype,n,ncand", [(F32, 5, 20), (F32, 28, 20), (F64, 12, 1030),
+                                           (F64, 20, 520)])
+def test_cost_without_a_trace_of_the_start_state(oracle_lib, E, dtype, n, ncand):
+    """A model that contracts to 1e-4 in one step: the cost sums x_1 .. x_T only,
+    so x_0, whose square is 1e8 times the others', may leave no rounding in it.
+    Bounds: (n + T + 20) roundings of positive terms; half a unit in the last
+    place of x_0's square would be 1e8 of them."""
+    m, T, p, u = 3, 6, 2, 2.0**-24 if dtype == F32 else 2.0**-53
+    npd = np.float32 if dtype == F32 else np.float64
+    rng = np.random.default_rng(n)
+    A = rng.normal(0, 1, (n, n))
+    A *= 1e-4 / np.linalg.norm(A, 2)
+    prob = W.Problem(model=W.LINEAR, n=n, m=m, T=T, p=p, Ad=A, Bd=1e-4 * rng.normal(0, 1, (n, m)),
+                     q=rng.uniform(0.5, 2, n), r=np.full(m, 1e-12), qf=rng.uniform(0.5, 2, n),
+                     x_goal=np.zeros(n), u_goal=np.zeros(m), u_min=-np.ones(m),
+                     u_max=np.ones(m)).cast(npd)
+    x0 = W.draw_x0(n, 3, scale=1.0).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 5).astype(npd).astype(np.float64)
+    K = dev(knots, dtype)
+    dJ, cost = torch.empty_like(K), dev(np.full(ncand, np.nan), dtype)
+    E.empc_grad(E.DeviceProblem(prob, dtype), dev(x0, dtype), K, ncand, ncand, dJ, cost)
+    want = oracle_lib.rollout_cost(prob, x0, knots, ncand)
+    err = np.abs(cost.cpu().numpy().astype(np.float64) / want - 1.0)
+    # the states' own rounding: n + m products summed, doubled by the square
+    assert err.max() < 2 * (n + T + 20 + n + m) * u * 4
