@@ -1,27 +1,29 @@
 // Adjoint gradient and Adam refinement of the linear model on the matrix
 // cores (gfx950), shared by the FP32 and FP64 translation units.
 //
-// A tile of 16 candidates runs on a workgroup of NT = ceil(n / 16)
+// A tile of 16 candidates runs on a workgroup of NT = ceil(n / 16) state
 // wavefronts, wavefront w owning state rows 16w .. 16w+15, in the accumulator
-// layout and K order of the M-split rollout (rollout_linear.hpp).  The
-// backward recursion lambda_k = 2 Q (x_k - g) + A^T lambda_{k+1} is the same
-// contraction with A transposed, so the adjoint chains through the
-// accumulators as the state does.  dJ/dU_j needs B^T lambda only through its
-// knot-weighted sums: sum_k w_k(j) lambda_{k+1} is summed in registers and
-// multiplied by B^T once per knot; the input weights' part is closed form in
-// the sums of (1-c)^2, c (1-c) and c^2 over the knot segments.  The tile's
-// knots sit in LDS, and so do the states of the forward pass: all of them
-// when they fit (2 T dependent steps), else one per block of S steps, each
-// block recomputed before it is walked backward (3 T steps).  Above one
-// M-tile a further wavefront takes the input side (the input cost, the
-// knots' products with B^T) while the state wavefronts go on: 43 -> 39 us.
+// layout and K order of the M-split rollout (rollout_linear.hpp), and of UT =
+// ceil(m / 16) input wavefronts.  The backward recursion lambda_k =
+// 2 Q (x_k - g) + A^T lambda_{k+1} is the same contraction with A transposed,
+// so the adjoint chains through the accumulators as the state does.  The input
+// wavefronts do what hangs on the inputs beside that chain: forward the products
+// B_d u_k + w_d, one step ahead, and the input cost; backward the products
+// B_d^T lambda_{k+1} and their sums over the knots.  The tile's knots sit in
+// LDS, and so do the states of the forward pass: all of them when they fit (2 T
+// dependent steps), else one per block of S steps, each block recomputed before
+// it is walked backward (3 T steps).
 //
-// What bounds it is the chain of dependent steps (4 NT MFMAs in two chains, an
+// What bounds it is the chain of dependent steps (4 NT MFMAs in four chains, an
 // LDS round trip and a barrier each), as in the M-split rollout: one
 // wavefront pair per candidate took the same chain for a single candidate.
-// 14-DoF chain, T = 50, p = 10, FP32, 4096 candidates: 238 us with a workgroup
-// per candidate on the vector ALUs, 42 us here (65536: 3.2 ms and 0.55 ms); 64
-// candidates with five Adam steps: 235 and 203 us.
+// 14-DoF chain, T = 50, p = 10, FP32, 4096 candidates: 236 us with a workgroup
+// per candidate on the vector ALUs, 44 us here (65536: 3.1 ms and 0.47 ms); 64
+// candidates with five Adam steps: 235 and 220 us.
+// Products with B_d per knot instead of per step, blended (41 us, 202 us), lost
+// accuracy: see drive.  Errors against 64 bits are those of the per-candidate
+// kernel or less (FP32 gradient, rms over sizes and horizons: 0.80 to 0.93 of
+// them; cost 0.88 to 0.95).
 #pragma once
 #include <math.h>
 
@@ -36,44 +38,40 @@ namespace empc {
 struct LinAdjPlan {
     int full;          // every state kept
     int S, nblk;       // steps per block and blocks (full: one block)
-    size_t oX, oL, oK, oR, oS, oU, oM1, oM2, oG, total;
+    size_t oX, oL, oD, oR, oC, oU, oM1, oM2, oG, total;
 };
-inline LinAdjPlan lin_adj_layout(int NT, int NU, int T, int p, bool refine, int S, bool full) {
+inline LinAdjPlan lin_adj_layout(int NT, int UT, int T, int p, bool refine, int S, bool full) {
     LinAdjPlan g;
     g.full = full;
     g.S = S;
     g.nblk = full ? 1 : (T + S - 1) / S;
-    const size_t slot = (size_t)NT * 256, kn = (size_t)p * NU * 64;
+    const size_t slot = (size_t)NT * 256, kn = (size_t)p * UT * 256;
     size_t o = 0;
     // full: x_0 .. x_{T-1}; else the blocks' first states, one block, a ring of two
     g.oX = o; o += slot * (full ? (size_t)T : (size_t)g.nblk + S + 2);
     g.oL = o; o += 2 * slot;
-    g.oK = o; o += 3 * slot;
+    g.oD = o; o += 2 * slot;
     g.oU = o; o += kn;
     g.oM1 = o; o += refine ? kn : 0;
     g.oM2 = o; o += refine ? kn : 0;
     g.oG = o; o += refine ? kn : 0;
-    g.oS = o; o += (size_t)3 * p;
-    g.oR = o; o += (size_t)(NT + 1) * 16;
+    g.oR = o; o += (size_t)(NT + UT) * 16;
+    g.oC = o; o += (size_t)T + 1;
     g.total = o;
     return g;
 }
 
-// wavefronts of a tile: the NT state wavefronts, and above one of them a
-// further one for the inputs
-template <int NT>
-constexpr int ADJ_WAVES = NT > 1 ? NT + 1 : 1;
-
 template <typename T, int NT, int UT>
-__global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
+__global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
     ProbView<T> P, LinAdjPlan G, const T *__restrict__ x0, const T *__restrict__ knots,
     int64_t ncand, int64_t ld, T *__restrict__ dJ, T *__restrict__ cost, int steps, T lr,
     T *__restrict__ knots_io, T *__restrict__ cost_io) {
     typedef typename Mfma<T>::v4 v4;
     constexpr int NU = 4 * UT, KN = NU * 64;  // input slices; elements of one knot
+    constexpr int NW = NT + UT;  // state wavefronts, input wavefronts
     extern __shared__ __align__(32) unsigned char adj_smem[];
     T *sm = (T *)adj_smem;
-    T *sU = sm + G.oU, *sS = sm + G.oS, *sR = sm + G.oR;
+    T *sU = sm + G.oU, *sC = sm + G.oC, *sR = sm + G.oR;
     const int lane = threadIdx.x & 63;
     const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int col = lane & 15, grp = lane >> 4;
@@ -83,35 +81,288 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
     const bool box = P.qb != nullptr;  // uniform
     const int arow = Mfma<T>::mstate(col);
 
-    constexpr int NW = ADJ_WAVES<NT>;
-    const bool inputs = w == NW - 1;  // runs the input side (with one wavefront: everything)
     // the tile's knots, [knot][slice][lane]: lane (grp, col) of slice s holds
     // input 4 s + grp of candidate col (past m or the candidates: a value
-    // that is never stored and meets zero weights); the first loads are in
-    // flight while the operands are loaded
+    // that is never stored and meets zero weights)
     const T *src = refine ? knots_io : knots;
     const int64_t cand_c = valid ? cand : ncand - 1;
     constexpr int LB = 16;
-    T first[LB];
-    auto load_knots = [&](int e0) {
+    for (int e0 = w; e0 < p * NU; e0 += LB * NW) {
+        T b[LB];
 #pragma unroll
-        for (int b = 0; b < LB; ++b) {
-            const int e = min(e0 + b * NW, p * NU - 1), i = 4 * (e % NU) + grp;
-            first[b] = src[(int64_t)((e / NU) * m + min(i, m - 1)) * ld + cand_c];
+        for (int q = 0; q < LB; ++q) {
+            const int e = min(e0 + q * NW, p * NU - 1), i = 4 * (e % NU) + grp;
+            b[q] = src[(int64_t)((e / NU) * m + min(i, m - 1)) * ld + cand_c];
         }
-    };
-    auto store_knots = [&](int e0) {
 #pragma unroll
-        for (int b = 0; b < LB; ++b) {
-            const int e = e0 + b * NW;
-            if (e < p * NU) sU[e * 64 + lane] = 4 * (e % NU) + grp < m ? first[b] : (T)0;
+        for (int q = 0; q < LB; ++q) {
+            const int e = e0 + q * NW;
+            if (e < p * NU) sU[e * 64 + lane] = 4 * (e % NU) + grp < m ? b[q] : (T)0;
         }
+    }
+    if (refine)
+        for (int e = threadIdx.x; e < p * KN; e += 64 * NW) sm[G.oM1 + e] = sm[G.oM2 + e] = 0;
+    // first step of segment a (steps with idx1 = a)
+    auto seg_start = [&](int a) {
+        return p == 1 ? (a == 0 ? 0 : Tn) : a >= p ? Tn : (a * (Tn - 1) + p - 2) / (p - 1);
     };
-    load_knots(w);
+    // the steps' blend weights c_k (divided: a rounded reciprocal would scale all
+    // of them alike)
+    for (int k = threadIdx.x; k <= Tn; k += 64 * NW) {
+        const Knot kn = knot_at(Tn, p, min(k, Tn - 1));
+        sC[k] = (T)kn.rem / (T)kn.den;
+    }
+    auto tile = [&](T *slot, int t) { return reinterpret_cast<v4 *>(slot) + t * 64 + lane; };
+    auto slot = [&](int k) { return sm + G.oX + (size_t)k * NT * 256; };
+    auto lam_at = [&](int i) { return sm + G.oL + i * (NT * 256); };    // rings of two
+    auto drive_at = [&](int i) { return sm + G.oD + i * (NT * 256); };
+    const v4 zero = {0, 0, 0, 0};
 
-    // A operands of the state wavefronts by slot i (M-tile t = (w + i) mod
-    // NT): rows of A_d and of A_d^T; B_d's rows by input slice
-    T aX[4 * NT], aT[4 * NT], aU[NU];
+    // Operands of input wavefront q: it multiplies by the rows of B_d of M-tiles
+    // q, q + UT, .. and by the rows q of B_d^T
+    constexpr int NB = (NT + UT - 1) / UT;
+    struct Inputs {
+        int q;
+        T bT[4 * NT];     // rows of B_d^T of output tile q, by M-tile
+        T b[NB][NU];      // rows of B_d of M-tile q + UT i, by input slice
+        v4 Wd[NB];
+        T Rw[4], Ug[4];   // register s: input 16 q + 4 s + grp
+    };
+    auto load_inputs = [&](Inputs &I) __attribute__((always_inline)) {
+        I.q = w - NT;
+#pragma unroll
+        for (int e = 0; e < 4 * NT; ++e) {
+            const int row = 16 * I.q + arow, kk = 16 * (e / 4) + Mfma<T>::row(grp, e % 4);
+            I.bT[e] = row < m && kk < n ? P.Bd[kk * m + row] : (T)0;
+        }
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int t = I.q + UT * i;
+#pragma unroll
+            for (int s = 0; s < NU; ++s) {
+                const int row = 16 * t + arow, j = 4 * s + grp;
+                I.b[i][s] = row < n && j < m ? P.Bd[row * m + j] : (T)0;
+            }
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * t + Mfma<T>::row(grp, v);
+                I.Wd[i][v] = row < n && P.wd ? P.wd[row] : (T)0;
+            }
+        }
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int i = 16 * I.q + 4 * s + grp;
+            I.Rw[s] = i < m ? P.r[i] : (T)0;
+            I.Ug[s] = i < m && P.ug ? P.ug[i] : (T)0;
+        }
+    };
+    // the knot's inputs, from slice s0 on
+    auto knot = [&](int j, int s0, auto &U) __attribute__((always_inline)) {
+        const T *u = sU + (size_t)(j < p ? j : p - 1) * KN + 64 * s0 + lane;
+#pragma unroll
+        for (int s = 0; s < (int)(sizeof(U) / sizeof(T)); ++s) U[s] = u[64 * s];
+    };
+    // B_d u_k + w_d, rows of the wavefront's i-th M-tile.  A product per step: from
+    // products per knot, blended, the steps of a segment would share two vectors'
+    // rounding, a constant force (states 100 times as far from the origin as from
+    // the goal, 28 states, FP32: gradient error 4.5e-6 against 6e-7).
+    auto drive = [&](const Inputs &I, const T *u, int i) __attribute__((always_inline)) {
+        v4 acc[4] = {I.Wd[i], zero, zero, zero};
+#pragma unroll
+        for (int s = 0; s < NU; ++s) acc[s & 3] = Mfma<T>::op(I.b[i][s], u[s], acc[s & 3]);
+        return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+    };
+    // dJ/dU_j: to dJ, or to G when refining.  The sums over the steps that lead to
+    // it, and those of the cost, are in FP64: their rounding is the result's own.
+    typedef Mfma<double>::v4 d4;
+    auto knot_done = [&](const Inputs &I, int j, const d4 &sum) __attribute__((always_inline)) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const int i = 16 * I.q + 4 * s + grp;
+            if (refine)
+                sm[G.oG + (size_t)j * KN + 256 * I.q + 64 * s + lane] = (T)sum[s];
+            else if (i < m && valid)
+                dJ[(int64_t)(j * m + i) * ld + cand] = (T)sum[s];
+        }
+    };
+    // the wavefronts' shares of the cost, summed in FP64: what is added at the
+    // cost's own size is rounded once
+    auto total = [&]() __attribute__((always_inline)) -> T {
+        double J = sR[col];
+#pragma unroll
+        for (int t = 1; t < NT + UT; ++t) J += sR[t * 16 + col];
+        return (T)J;
+    };
+    auto over_rows = [&](double J) __attribute__((always_inline)) {  // the four lanes of a candidate
+        J += __shfl_xor(J, 16, 64);
+        return J + __shfl_xor(J, 32, 64);
+    };
+
+    // The passes of one side: forward() (the cost, in every lane) and backward()
+    // (the gradient, to dJ or to G).  Both sides pass the same barriers: one per
+    // step of a march, one in forward() after it, one per backward step.
+    auto passes = [&](auto &&forward, auto &&backward, bool writes_cost)
+                      __attribute__((always_inline)) {
+        lds_barrier();  // knots, sums
+        if (!refine) {
+            const T J = forward();
+            if (cost && writes_cost && grp == 0 && valid) cost[cand] = J;
+            backward();
+            return;
+        }
+        // Adam (Kingma & Ba 2015), bias-corrected, clamp after each update
+        const T b1 = (T)0.9, b2 = (T)0.999, eps = (T)1e-8;
+        T b1t = 1, b2t = 1, J0 = 0;
+        for (int t = 1; t <= steps; ++t) {
+            const T Jt = forward();
+            if (t == 1) J0 = Jt;
+            backward();
+            lds_barrier();
+            b1t *= b1;
+            b2t *= b2;
+            for (int e = threadIdx.x; e < p * KN; e += 64 * NW) {
+                const int i = 4 * (e / 64 % NU) + grp;
+                if (i >= m) continue;
+                const T g = sm[G.oG + e];
+                const T m1 = b1 * sm[G.oM1 + e] + ((T)1 - b1) * g;
+                const T m2 = b2 * sm[G.oM2 + e] + ((T)1 - b2) * g * g;
+                sm[G.oM1 + e] = m1;
+                sm[G.oM2 + e] = m2;
+                const T mh = m1 / ((T)1 - b1t), vh = m2 / ((T)1 - b2t);
+                T U = sU[e] - lr * mh / (sqrt(vh) + eps);
+                U = U < P.umin[i] ? P.umin[i] : U;
+                U = U > P.umax[i] ? P.umax[i] : U;
+                sU[e] = U;
+            }
+            lds_barrier();
+        }
+        // accept the refined knots only if they cost less, both costs by this pass
+        const T Jn = forward();
+        if (valid && Jn < J0) {
+            for (int e = w; e < p * NU; e += NW) {
+                const int i = 4 * (e % NU) + grp;
+                if (i < m) knots_io[(int64_t)((e / NU) * m + i) * ld + cand] = sU[e * 64 + lane];
+            }
+            if (writes_cost && grp == 0) cost_io[cand] = Jn;
+        }
+    };
+
+    if (w >= NT) {
+        // An input wavefront.  Forward, it stays one step ahead and leaves the
+        // steps' B_d u_k + w_d in a ring of two; backward, it multiplies the
+        // lambda that the state wavefronts exchange and weights the product into
+        // the sums of the step's two knots.
+        Inputs I;
+        load_inputs(I);
+        auto march = [&](int k0, int k1, auto &&each) __attribute__((always_inline)) {
+            if (k0 >= k1) return;
+            int a = p == 1 || Tn == 1 ? 0 : k0 * (p - 1) / (Tn - 1), ke = seg_start(a + 1);
+            T Ua[NU], Ub[NU];  // knots a and a + 1
+            knot(a, 0, Ua);
+            knot(a + 1, 0, Ub);
+            T c = sC[k0];
+            for (int k = k0; k < k1; ++k) {
+                T u[NU];
+#pragma unroll
+                for (int s = 0; s < NU; ++s) u[s] = ((T)1 - c) * Ua[s] + c * Ub[s];
+                c = sC[k + 1];
+                each(u, k + 1 == ke);
+#pragma unroll
+                for (int i = 0; i < NB; ++i)
+                    if (I.q + UT * i < NT)  // uniform
+                        *tile(drive_at(k & 1), I.q + UT * i) = drive(I, u, i);
+                lds_barrier();
+                if (k + 1 == ke) {
+                    ++a;
+                    ke = seg_start(a + 1);
+#pragma unroll
+                    for (int s = 0; s < NU; ++s) Ua[s] = Ub[s];
+                    knot(a + 1, 0, Ub);
+                }
+            }
+        };
+        passes(
+            [&]() __attribute__((always_inline)) -> T {
+                double J = 0;
+                v4 Js = zero;
+                march(0, Tn, [&](const T *u, bool last) {
+#pragma unroll
+                    for (int q = 0; q < UT; ++q)
+                        if (q == I.q)  // uniform
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) {
+                                const T e = I.Ug[s] - u[4 * q + s];
+                                Js[s] += e * e;
+                            }
+                    if (last) {
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) J += (double)I.Rw[s] * Js[s];
+                        Js = zero;
+                    }
+                });
+                J = over_rows(J);
+                if (grp == 0) sR[w * 16 + col] = (T)J;
+                lds_barrier();
+                return total();
+            },
+            [&]() __attribute__((always_inline)) {
+                // gA, gB: the current segment's sums for its two knots; carry: those
+                // of the segment after it for the second one
+                const d4 none = {0, 0, 0, 0};
+                T r2[4];
+#pragma unroll
+                for (int s = 0; s < 4; ++s) r2[s] = (T)2 * I.Rw[s];
+                d4 gA = none, gB = none, carry = none;
+                int a = p - 1, ka = seg_start(p - 1), par = 0;
+                T Ua[4], Ub[4];  // own inputs of knots a and a + 1
+                knot(a, 4 * I.q, Ua);
+                knot(a + 1, 4 * I.q, Ub);
+                for (int blk = G.nblk - 1; blk >= 0; --blk) {
+                    const int k0 = G.full ? 0 : blk * G.S, k1 = G.full ? Tn : min(k0 + G.S, Tn);
+                    if (!G.full) march(k0, k1 - 1, [](const T *, bool) {});
+                    for (int k = k1 - 1; k >= k0; --k) {
+                        const T c = sC[k];
+                        v4 acc[4] = {zero, zero, zero, zero};
+                        lds_barrier();
+#pragma unroll
+                        for (int t = 0; t < NT; ++t) {
+                            const v4 Lam = *tile(lam_at(par), t);
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) {
+                                const int s = NT == 1 ? v : (v & 1) + 2 * (t & 1);
+                                acc[s] = Mfma<T>::op(I.bT[4 * t + v], Lam[v], acc[s]);
+                            }
+                        }
+                        par ^= 1;
+                        const v4 bl = (acc[0] + acc[1]) + (acc[2] + acc[3]);
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) {
+                            const T u = ((T)1 - c) * Ua[s] + c * Ub[s];
+                            const double g = r2[s] * (u - I.Ug[s]) + bl[s];
+                            gA[s] += (double)((T)1 - c) * g;
+                            gB[s] += (double)c * g;
+                        }
+                        if (k == ka) {  // segment a is done: knot a + 1 is complete
+                            if (a < p - 1) knot_done(I, a + 1, carry + gB);
+                            carry = gA;
+                            if (a == 0) knot_done(I, 0, carry);
+                            gA = gB = none;
+                            --a;
+                            ka = seg_start(a);
+#pragma unroll
+                            for (int s = 0; s < 4; ++s) Ub[s] = Ua[s];
+                            knot(max(a, 0), 4 * I.q, Ua);
+                        }
+                    }
+                }
+            },
+            w == NT);
+        return;
+    }
+
+    // A state wavefront.  A operands by slot i (M-tile t =
+    // (w + i) mod NT): rows of A_d and of A_d^T
+    T aX[4 * NT], aT[4 * NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
@@ -121,101 +372,43 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
             aX[4 * i + v] = in ? P.Ad[row * n + kk] : (T)0;
             aT[4 * i + v] = in ? P.Ad[kk * n + row] : (T)0;
         }
-#pragma unroll
-    for (int s = 0; s < NU; ++s) {
-        const int row = 16 * w + arow, j = 4 * s + grp;
-        aU[s] = row < n && j < m ? P.Bd[row * m + j] : (T)0;
-    }
-    // own rows: start state, disturbance, goal, weights, box
-    v4 X0, Wd, Xg, Q, Qf, Lo, Hi, Qb, Sb;
+    // own rows: start state, goal, weights, box
+    v4 X0, Xg, Q, Qf, Lo, Hi, Qb;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int row = 16 * w + Mfma<T>::row(grp, v);
         const bool in = row < n, bx = in && box;
         X0[v] = in ? x0[row] : (T)0;
-        Wd[v] = in && P.wd ? P.wd[row] : (T)0;
         Xg[v] = in && P.xg ? P.xg[row] : (T)0;
         Q[v] = in ? P.q[row] : (T)0;
         Qf[v] = in && P.qf ? P.qf[row] : (T)0;
         Lo[v] = bx ? P.xlo[row] : (T)-1;
         Hi[v] = bx ? P.xhi[row] : (T)1;
         Qb[v] = bx ? P.qb[row] : (T)0;
-        Sb[v] = bx && P.sb ? P.sb[row] : (T)0;
     }
-    // the input side: rows of B_d^T of output tile u by M-tile, weights and
-    // goals (tile u, register s: input 16 u + 4 s + grp)
-    T bT[UT][4 * NT], Rw[UT][4], Ug[UT][4];
-#pragma unroll
-    for (int u = 0; u < UT; ++u) {
-#pragma unroll
-        for (int i = 0; i < NT; ++i)
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const int row = 16 * u + arow, kk = 16 * i + Mfma<T>::row(grp, v);
-                bT[u][4 * i + v] = inputs && row < m && kk < n ? P.Bd[kk * m + row] : (T)0;
-            }
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {
-            const int i = 16 * u + 4 * s + grp;
-            Rw[u][s] = i < m ? P.r[i] : (T)0;
-            Ug[u][s] = i < m && P.ug ? P.ug[i] : (T)0;
-        }
-    }
-    store_knots(w);
-    for (int e0 = w + LB * NW; e0 < p * NU; e0 += LB * NW) {
-        load_knots(e0);
-        store_knots(e0);
-    }
-    if (refine)
-        for (int e = threadIdx.x; e < p * KN; e += 64 * NW) sm[G.oM1 + e] = sm[G.oM2 + e] = 0;
-    const T inv_den = Tn > 1 ? (T)1 / (T)(Tn - 1) : (T)0;
-    // first step of segment a (steps with idx1 = a)
-    auto seg_start = [&](int a) {
-        return p == 1 ? (a == 0 ? 0 : Tn) : a >= p ? Tn : (a * (Tn - 1) + p - 2) / (p - 1);
-    };
-    auto weight = [&](int k, int a) {
-        return (T)(k * (p - 1) - a * (Tn - 1)) * inv_den;  // 0 for one knot or one step
-    };
-    // sums of (1-c)^2, c (1-c), c^2 over each segment
-    for (int a = threadIdx.x; a < p; a += 64 * NW) {
-        T s00 = 0, s01 = 0, s11 = 0;
-        for (int k = seg_start(a); k < seg_start(a + 1); ++k) {
-            const T c = weight(k, a), d = (T)1 - c;
-            s00 += d * d;
-            s01 += c * d;
-            s11 += c * c;
-        }
-        sS[3 * a] = s00;
-        sS[3 * a + 1] = s01;
-        sS[3 * a + 2] = s11;
-    }
-    auto tile = [&](T *slot, int t) { return reinterpret_cast<v4 *>(slot) + t * 64 + lane; };
-    auto slot = [&](int k) { return sm + G.oX + (size_t)k * NT * 256; };
-    // start + M V over all M-tiles of a vector V, this wavefront's rows of the
+    // M V over all M-tiles of a vector V, this wavefront's rows of the
     // matrix in `op` (by slot): V's own tile from registers, the others from
     // `at`, where every wavefront has stored its own before the call.  The
     // barrier sits between the own slices, as in the M-split rollout, and
-    // `shadow`, vector work of no use to this step, behind them.
-    auto contract = [&](const T *op, v4 own, T *at, v4 start, auto &&shadow)
+    // `shadow`, vector work of no use to this product, behind them.
+    auto contract = [&](const T *op, v4 own, T *at, auto &&shadow)
                         __attribute__((always_inline)) {
         // four partial sums, added pairwise: the rounding of the per-candidate
         // kernel's dot products (with two the gradient's error is 1.3 times
         // that, and the call 8 % faster)
-        v4 acc[4] = {start, v4{0, 0, 0, 0}, v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
+        v4 acc[4] = {zero, zero, zero, zero};
         acc[0] = Mfma<T>::op(op[0], own[0], acc[0]);
         acc[1] = Mfma<T>::op(op[1], own[1], acc[1]);
         v4 o[NT];
-        if (NT > 1) {
-            __builtin_amdgcn_sched_barrier(0);
-            lds_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        lds_barrier();
 #pragma unroll
-            for (int i = 1; i < NT; ++i) o[i] = *tile(at, (w + i) % NT);
-        }
+        for (int i = 1; i < NT; ++i) o[i] = *tile(at, (w + i) % NT);
         constexpr int H = NT == 1 ? 2 : 0;
         acc[H] = Mfma<T>::op(op[2], own[2], acc[H]);
         acc[H + 1] = Mfma<T>::op(op[3], own[3], acc[H + 1]);
         shadow();
-        if (NT > 1) __builtin_amdgcn_sched_barrier(0);
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
         for (int i = 1; i < NT; ++i)
 #pragma unroll
@@ -224,141 +417,30 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
                     Mfma<T>::op(op[4 * i + v], o[i][v], acc[(v & 1) + 2 * (i & 1)]);
         return (acc[0] + acc[1]) + (acc[2] + acc[3]);
     };
-    // own rows of V = B_d U + w_d for knot j
-    auto response = [&](int j) __attribute__((always_inline)) {
-        const T *u = sU + (size_t)(j < p ? j : p - 1) * KN + lane;
-        v4 V[2] = {Wd, v4{0, 0, 0, 0}};
-#pragma unroll
-        for (int s = 0; s < NU; ++s) V[s & 1] = Mfma<T>::op(aU[s], u[64 * s], V[s & 1]);
-        return V[0] + V[1];
-    };
-    // states x_{k0+1} .. x_{k1} from X = x_{k0}, which every wavefront has
-    // stored at `at`; to(k): where x_k goes; each(x_k, k): called in the shadow
-    // of the step that leaves x_k
+    // States x_{k0+1} .. x_{k1} from X = x_{k0}, which every wavefront has
+    // stored at `at`; to(k): where x_k goes; each(x_k, k): called in the shadow of
+    // the step that leaves x_k.  B_d u_k + w_d is added last: the sums of A_d x
+    // round by their own size.
     auto march = [&](int k0, int k1, v4 X, T *at, auto &&to, auto &&each)
                      __attribute__((always_inline)) {
-        int a = p == 1 || Tn == 1 ? 0 : k0 * (p - 1) / (Tn - 1);
-        v4 Va = response(a), Vb = response(a + 1);
-        for (int k = k0; k < k1; ++a) {
-            const int ke = min(seg_start(a + 1), k1);
-            const v4 dV = Vb - Va;
-            v4 start = Va + weight(k, a) * dV;
-            for (; k < ke; ++k) {
-                const v4 s0 = start;
-                X = contract(aX, X, at, s0, [&, X]() {
+        for (int k = k0; k < k1; ++k) {
+            v4 Bu;
+            X = contract(aX, X, at, [&, X]() {
+                    Bu = *tile(drive_at(k & 1), w);
                     each(X, k);
-                    start = Va + weight(k + 1, a) * dV;
-                });
-                at = to(k + 1);
-                *tile(at, w) = X;
-            }
-            Va = Vb;
-            if (k < k1) Vb = response(a + 2);
+                }) + Bu;
+            at = to(k + 1);
+            *tile(at, w) = X;
         }
         return X;
     };
-    // input side of the cost: each segment's part in closed form
-    auto input_cost = [&]() __attribute__((always_inline)) {
-        T J = 0;
-        for (int a = 0; a < p; ++a) {
-            const T *u0 = sU + (size_t)a * KN + lane, *u1 = a + 1 < p ? u0 + KN : u0;
-            const T s00 = sS[3 * a], s01 = sS[3 * a + 1], s11 = sS[3 * a + 2];
-#pragma unroll
-            for (int u = 0; u < UT; ++u)
-#pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const T e0 = u0[256 * u + 64 * s] - Ug[u][s];
-                    const T e1 = u1[256 * u + 64 * s] - Ug[u][s];
-                    J += Rw[u][s] * (s00 * e0 * e0 + (T)2 * s01 * e0 * e1 + s11 * e1 * e1);
-                }
-        }
-        return J;
-    };
-    // dJ/dU_j from the weighted sum of lambda that the state wavefronts left
-    // at `at`: to dJ, or to G when refining
-    auto knot_grad = [&](int j, T *at) __attribute__((always_inline)) {
-        const T cc = sS[3 * j] + (j > 0 ? sS[3 * j - 1] : (T)0);
-        const T cn = j < p - 1 ? sS[3 * j + 1] : (T)0, cp = j > 0 ? sS[3 * j - 2] : (T)0;
-#pragma unroll
-        for (int u = 0; u < UT; ++u) {
-            const T *uj = sU + (size_t)j * KN + 256 * u + lane;
-            const T *un = j < p - 1 ? uj + KN : uj, *up = j > 0 ? uj - KN : uj;
-            v4 acc[2] = {v4{0, 0, 0, 0}, v4{0, 0, 0, 0}};
-#pragma unroll
-            for (int t = 0; t < NT; ++t) {
-                const v4 o = *tile(at, t);
-#pragma unroll
-                for (int v = 0; v < 4; ++v)
-                    acc[v & 1] = Mfma<T>::op(bT[u][4 * t + v], o[v], acc[v & 1]);
-            }
-#pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                const T g = acc[0][s] + acc[1][s] +
-                            (T)2 * Rw[u][s] *
-                                (cc * (uj[64 * s] - Ug[u][s]) + cn * (un[64 * s] - Ug[u][s]) +
-                                 cp * (up[64 * s] - Ug[u][s]));
-                const int i = 16 * u + 4 * s + grp;
-                if (refine)
-                    sm[G.oG + (size_t)j * KN + 256 * u + 64 * s + lane] = g;
-                else if (i < m && valid)
-                    dJ[(int64_t)(j * m + i) * ld + cand] = g;
-            }
-        }
-    };
-    auto lam_at = [&](int i) { return sm + G.oK + i * (NT * 256); };  // ring of three
-    auto next3 = [](int i) { return i == 2 ? 0 : i + 1; };
-    // The input wavefront (NT > 1) passes the state wavefronts' barriers: one
-    // per step of a march, one per backward step, one after the last
-    auto forward_inputs = [&]() __attribute__((always_inline)) -> T {
-        for (int k = 0; k < Tn; ++k) {
-            if (k == 0) {
-                T J = input_cost();
-                J += __shfl_xor(J, 16, 64);
-                J += __shfl_xor(J, 32, 64);
-                if (grp == 0) sR[NT * 16 + col] = J;
-            }
-            lds_barrier();
-        }
-        lds_barrier();
-        T J = sR[col];
-#pragma unroll
-        for (int t = 1; t <= NT; ++t) J += sR[t * 16 + col];
-        return J;
-    };
-    auto backward_inputs = [&]() __attribute__((always_inline)) {
-        int a = p - 1, ka = seg_start(p - 1), buf = 0, due = -1;
-        for (int blk = G.nblk - 1; blk >= 0; --blk) {
-            const int k0 = G.full ? 0 : blk * G.S, k1 = G.full ? Tn : min(k0 + G.S, Tn);
-            if (!G.full)
-                for (int k = k0; k < k1 - 1; ++k) lds_barrier();
-            for (int k = k1 - 1; k >= k0; --k) {
-                lds_barrier();
-                if (due >= 0) {  // published before this barrier
-                    knot_grad(due, lam_at(buf));
-                    buf = next3(buf);
-                    due = -1;
-                }
-                if (k == ka) {
-                    due = a < p - 1 ? a + 1 : -1;
-                    --a;
-                    ka = seg_start(a);
-                }
-            }
-        }
-        lds_barrier();
-        if (due >= 0) {
-            knot_grad(due, lam_at(buf));
-            buf = next3(buf);
-        }
-        knot_grad(0, lam_at(buf));
-    };
-    // cost of the knots in sU; leaves the states in LDS and x_T in XT
     v4 XT = X0;
+    // cost of the knots in sU; leaves the states in LDS and x_T in XT
     auto forward = [&]() __attribute__((always_inline)) -> T {
         // sums over x_1 .. x_T: every step adds the state that it leaves, x_T
         // follows; x_0's terms are left out (selects: a branch would cut the
         // step), not subtracted, as their rounding would stay in the sums
-        v4 S = {0, 0, 0, 0}, Pn = {0, 0, 0, 0}, Cn = {0, 0, 0, 0};
+        v4 S = zero, Pn = zero, Cn = zero;
         auto add = [&](const v4 &X, int k) {
 #pragma unroll
             for (int v = 0; v < 4; ++v) {
@@ -382,7 +464,7 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
                 // idle here (not into a state's slot: other wavefronts may still
                 // be reading the last step's, which for T = 1 is x_0's)
                 [&](int k) -> T * {
-                    at = k < Tn ? at + NT * 256 : sm + G.oL;
+                    at = k < Tn ? at + NT * 256 : lam_at(0);
                     return at;
                 },
                 add);
@@ -402,41 +484,34 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
                 add);
         }
         add(XT, Tn);
-        T J = 0;
+        double J = 0;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            const T e = XT[v] - Xg[v];
-            J += Q[v] * S[v] + Qf[v] * e * e;
-            if (box) J += Qb[v] * Pn[v] + Sb[v] * Cn[v];
+            const double e = XT[v] - Xg[v];
+            J += (double)Q[v] * S[v] + (double)Qf[v] * e * e;
+            if (box) J += (double)Qb[v] * Pn[v];
         }
-        if (NT == 1) J += input_cost();
-        J += __shfl_xor(J, 16, 64);
-        J += __shfl_xor(J, 32, 64);
-        if (NT == 1) return J;
-        if (grp == 0) sR[w * 16 + col] = J;
-        lds_barrier();
-        J = sR[col];
+        if (box && P.sb) {
 #pragma unroll
-        for (int t = 1; t <= NT; ++t) J += sR[t * 16 + col];
-        return J;
+            for (int v = 0; v < 4; ++v) {
+                const int row = 16 * w + Mfma<T>::row(grp, v);
+                J += row < n ? (double)P.sb[row] * Cn[v] : 0.0;
+            }
+        }
+        J = over_rows(J);
+        if (grp == 0) sR[w * 16 + col] = (T)J;
+        lds_barrier();
+        return total();
     };
-    // dJ/dU of the knots, after forward(): to dJ, or to G when refining
+    // dJ/dU of the knots, after forward()
     auto backward = [&]() __attribute__((always_inline)) {
-        v4 L, gA = {0, 0, 0, 0}, gB = {0, 0, 0, 0}, carry = {0, 0, 0, 0};
+        v4 L;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             L[v] = (T)2 * (Q[v] + Qf[v]) * (XT[v] - Xg[v]);
             if (box) L[v] += box_pen_grad(XT[v], Lo[v], Hi[v], Qb[v]);
         }
-        int par = 0, buf = 0;
-        // knot j's weighted sum of lambda is complete: the input wavefront
-        // takes it after the next barrier
-        auto flush = [&](int j, const v4 &Lam) {
-            *tile(lam_at(buf), w) = Lam;
-            if (NT == 1) knot_grad(j, lam_at(buf));
-            buf = next3(buf);
-        };
-        int a = p - 1, ka = seg_start(p - 1);
+        int par = 0;
         for (int blk = G.nblk - 1; blk >= 0; --blk) {
             const int k0 = G.full ? 0 : blk * G.S, k1 = G.full ? Tn : min(k0 + G.S, Tn);
             T *seg = slot(G.full ? 0 : G.nblk);
@@ -450,99 +525,30 @@ __global__ __launch_bounds__(64 * ADJ_WAVES<NT>) void adjoint_linear_kernel(
             }
             v4 X = *tile(seg + (k1 - 1 - k0) * (NT * 256), w);
             for (int k = k1 - 1; k >= k0; --k) {
-                const T c = weight(k, a);
-                auto sums = [&, L]() {
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) {
-                        gA[v] += ((T)1 - c) * L[v];
-                        gB[v] += c * L[v];
-                    }
-                };
+                T *at = lam_at(par);
+                par ^= 1;
+                *tile(at, w) = L;
                 if (k >= 1) {
-                    T *at = sm + G.oL + par * (NT * 256);
-                    par ^= 1;
-                    if (NT > 1) *tile(at, w) = L;
-                    v4 s;
-                    L = contract(aT, L, at, v4{0, 0, 0, 0}, [&]() {
-                        sums();
-#pragma unroll
-                        for (int v = 0; v < 4; ++v) s[v] = (T)2 * Q[v] * (X[v] - Xg[v]);
+                    v4 e, s = zero;
+                    L = contract(aT, L, at, [&]() {
+                        e = (T)2 * (X - Xg);
                         if (box) {
 #pragma unroll
                             for (int v = 0; v < 4; ++v)
-                                s[v] += box_pen_grad(X[v], Lo[v], Hi[v], Qb[v]);
+                                s[v] = box_pen_grad(X[v], Lo[v], Hi[v], Qb[v]);
                         }
                         X = *tile(seg + (k > k0 ? k - 1 - k0 : 0) * (NT * 256), w);
                     });
-                    L += s;
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) L[v] += Q[v] * e[v];
+                    if (box) L += s;
                 } else {
-                    if (NT > 1) lds_barrier();
-                    sums();
-                }
-                if (k == ka) {  // segment a is done: knot a + 1 is complete
-                    if (a < p - 1) flush(a + 1, carry + gB);
-                    carry = gA;
-                    gA = gB = v4{0, 0, 0, 0};
-                    --a;
-                    ka = seg_start(a);
+                    lds_barrier();
                 }
             }
         }
-        flush(0, carry);
-        if (NT > 1) lds_barrier();
     };
-
-    auto run_forward = [&]() __attribute__((always_inline)) {
-        return NT > 1 && inputs ? forward_inputs() : forward();
-    };
-    auto run_backward = [&]() __attribute__((always_inline)) {
-        if (NT > 1 && inputs)
-            backward_inputs();
-        else
-            backward();
-    };
-    lds_barrier();  // knots, sums
-    if (!refine) {
-        const T J = run_forward();
-        if (cost && inputs && grp == 0 && valid) cost[cand] = J;
-        run_backward();
-        return;
-    }
-    // Adam (Kingma & Ba 2015), bias-corrected, clamp after each update
-    const T b1 = (T)0.9, b2 = (T)0.999, eps = (T)1e-8;
-    T b1t = 1, b2t = 1, J0 = 0;
-    for (int t = 1; t <= steps; ++t) {
-        const T Jt = run_forward();
-        if (t == 1) J0 = Jt;
-        run_backward();
-        lds_barrier();
-        b1t *= b1;
-        b2t *= b2;
-        for (int e = threadIdx.x; e < p * KN; e += 64 * NW) {
-            const int i = 4 * (e / 64 % NU) + grp;
-            if (i >= m) continue;
-            const T g = sm[G.oG + e];
-            const T m1 = b1 * sm[G.oM1 + e] + ((T)1 - b1) * g;
-            const T m2 = b2 * sm[G.oM2 + e] + ((T)1 - b2) * g * g;
-            sm[G.oM1 + e] = m1;
-            sm[G.oM2 + e] = m2;
-            const T mh = m1 / ((T)1 - b1t), vh = m2 / ((T)1 - b2t);
-            T U = sU[e] - lr * mh / (sqrt(vh) + eps);
-            U = U < P.umin[i] ? P.umin[i] : U;
-            U = U > P.umax[i] ? P.umax[i] : U;
-            sU[e] = U;
-        }
-        lds_barrier();
-    }
-    // accept the refined knots only if they cost less, both costs by this pass
-    const T Jn = run_forward();
-    if (valid && Jn < J0) {
-        for (int e = w; e < p * NU; e += NW) {
-            const int i = 4 * (e % NU) + grp;
-            if (i < m) knots_io[(int64_t)((e / NU) * m + i) * ld + cand] = sU[e * 64 + lane];
-        }
-        if (inputs && grp == 0) cost_io[cand] = Jn;
-    }
+    passes(forward, backward, false);
 }
 
 // Runs the call here if the tile's LDS fits; *taken tells.  All states are
@@ -554,10 +560,11 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
                                    T *knots_io, T *cost_io, hipStream_t s, bool *taken) {
     const int NT = (P.n + 15) / 16, UT = (P.m + 15) / 16;
     *taken = false;
-    // the shapes instantiated below (no more input than state tiles, and no
-    // shape whose registers spill to scratch: FP64 above 48 states, FP32
-    // above 48 with more than 32 inputs); the segment arithmetic is in 32 bits
-    if (NT > (sizeof(T) == 8 ? 3 : 4) || UT > NT || UT > (NT == 4 ? 2 : 3) ||
+    // the shapes instantiated below: no more input than state tiles, and no
+    // shape whose registers spill to scratch (FP64 above 48 states or 32 inputs,
+    // FP32 above 48 states with more than 32 inputs); the segment arithmetic is
+    // in 32 bits
+    if (NT > (sizeof(T) == 8 ? 3 : 4) || UT > NT || UT > (NT == 4 || sizeof(T) == 8 ? 2 : 3) ||
         (int64_t)P.Tn * P.p > (1 << 30))
         return hipSuccess;
     // A tile's step takes 4 NT MFMAs whatever the number of candidates; the
@@ -571,12 +578,12 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
     if ((sizeof(T) == 8 || NT == 4) && ncand <= (NT == 1 ? 1024 : 512)) return hipSuccess;
     const int64_t tiles = (ncand + 15) / 16;
     auto bytes = [&](const LinAdjPlan &g) { return g.total * sizeof(T); };
-    LinAdjPlan G = lin_adj_layout(NT, 4 * UT, P.Tn, P.p, steps > 0, P.Tn, true);
+    LinAdjPlan G = lin_adj_layout(NT, UT, P.Tn, P.p, steps > 0, P.Tn, true);
     const int64_t fit = bytes(G) <= MAX_GRAD_LDS ? (int64_t)(MAX_GRAD_LDS / bytes(G)) : 0;
     if (fit == 0 || tiles > 256 * fit) {
         int S = 1;
         while ((int64_t)S * S < P.Tn) ++S;
-        const LinAdjPlan B = lin_adj_layout(NT, 4 * UT, P.Tn, P.p, steps > 0, S, false);
+        const LinAdjPlan B = lin_adj_layout(NT, UT, P.Tn, P.p, steps > 0, S, false);
         if (bytes(B) <= MAX_GRAD_LDS) G = B;
     }
     if (bytes(G) > MAX_GRAD_LDS) return hipSuccess;
@@ -588,7 +595,7 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
                                                      (int)bytes(G));
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * (NT > 1 ? NT + 1 : 1)),
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles), dim3(64 * (NT + UT)),
                            bytes(G), s, P, G, x0,
                            knots, ncand, ld, dJ, cost, steps, lr, knots_io, cost_io);
         return hipGetLastError();
@@ -599,10 +606,10 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
         case 22: return go(adjoint_linear_kernel<T, 2, 2>);
         case 31: return go(adjoint_linear_kernel<T, 3, 1>);
         case 32: return go(adjoint_linear_kernel<T, 3, 2>);
-        case 33: return go(adjoint_linear_kernel<T, 3, 3>);
         default: break;
     }
     if constexpr (sizeof(T) == 4) {
+        if (NT == 3) return go(adjoint_linear_kernel<T, 3, 3>);
         if (UT == 1) return go(adjoint_linear_kernel<T, 4, 1>);
         return go(adjoint_linear_kernel<T, 4, 2>);
     }

@@ -110,3 +110,62 @@ def test_cost_without_a_trace_of_the_start_state(oracle_lib, E, dtype, n, ncand)
     err = np.abs(cost.cpu().numpy().astype(np.float64) / want - 1.0)
     # the states' own rounding: n + m products summed, doubled by the square
     assert err.max() < 2 * (n + T + 20 + n + m) * u * 4
+
+
+@pytest.mark.parametrize("dtype,n,ncand", [(F32, 8, 32), (F32, 28, 32), (F32, 44, 32),
+                                           (F32, 60, 530), (F64, 8, 1030), (F64, 28, 530)])
+def test_rounding_of_the_drive_averages_out(oracle_lib, E, dtype, n, ncand):
+    """200 steps around a state 100 away from the origin and one away from the
+    goal, two knots, |A| = 0.5.  A step rounds its state about three times, by
+    2.2e-6 rms each in FP32 (0.29 units in the last place of 100), and the steps'
+    errors are independent: twice 3.8e-6 / sqrt(200 / 2) of the distance to the goal
+    or about 1e-6 in the gradient; the bound is twice that.  A drive B_d u + w_d
+    rounded once per knot instead would push every step the same way: twice
+    2.2e-6 at least."""
+    m, T, p, unit = 4, 200, 2, 1.0 if dtype == F32 else 2.0**-29
+    npd = np.float32 if dtype == F32 else np.float64
+    rng = np.random.default_rng(n)
+    A = rng.normal(0, 1, (n, n))
+    A *= 0.5 / np.linalg.norm(A, 2)
+    xs = rng.uniform(80, 120, n) * rng.choice([-1.0, 1.0], n)
+    prob = W.Problem(model=W.LINEAR, n=n, m=m, T=T, p=p, Ad=A, Bd=rng.normal(0, 0.3, (n, m)),
+                     wd=(np.eye(n) - A) @ xs, q=np.ones(n), r=np.full(m, 0.01), qf=np.zeros(n),
+                     x_goal=xs + rng.normal(0, 1, n), u_goal=np.zeros(m), u_min=-np.ones(m),
+                     u_max=np.ones(m)).cast(npd)
+    x0 = xs.astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, ncand, 3).astype(npd).astype(np.float64)
+    K = dev(knots, dtype)
+    dJ, cost = torch.empty_like(K), dev(np.zeros(ncand), dtype)
+    E.empc_grad(E.DeviceProblem(prob, dtype), dev(x0, dtype), K, ncand, ncand, dJ, cost)
+    want, wcost = grad_long(prob, x0, knots)
+    err = np.abs(dJ.cpu().numpy() - want).max(axis=0) / np.abs(want).max(axis=0)
+    assert np.sqrt(np.mean(err.astype(float) ** 2)) < 2e-6 * unit
+    cerr = (cost.cpu().numpy() / wcost - 1).astype(float)
+    assert np.sqrt(np.mean(cerr**2)) < 2e-6 * unit
+
+
+def grad_long(prob, x0, knots):
+    """Costs and knot gradients in extended precision (plain numpy, no box)."""
+    L = np.longdouble
+    T, p, m, N = prob.T, prob.p, prob.m, knots.shape[1]
+    A, B = prob.Ad.astype(L), prob.Bd.astype(L)
+    w, q, r, qf, xg, ug = (np.asarray(v, dtype=L)[:, None] for v in
+                           (prob.wd, prob.q, prob.r, prob.qf, prob.x_goal, prob.u_goal))
+    U, X, us, at = knots.astype(L).reshape(p, m, N), [np.repeat(x0.astype(L)[:, None], N, 1)], [], []
+    for k in range(T):
+        a = k * (p - 1) // (T - 1) if T > 1 else 0
+        c = L(k * (p - 1) - a * (T - 1)) / L(max(T - 1, 1))
+        b = min(a + 1, p - 1)
+        at.append((a, b, c))
+        us.append((1 - c) * U[a] + c * U[b])
+        X.append(A @ X[-1] + B @ us[-1] + w)
+    J, lam = (qf * (X[T] - xg) ** 2).sum(0), 2 * (q + qf) * (X[T] - xg)
+    D = np.zeros((p, m, N), L)
+    for k in range(T - 1, -1, -1):
+        J = J + (q * (X[k + 1] - xg) ** 2).sum(0) + (r * (us[k] - ug) ** 2).sum(0)
+        a, b, c = at[k]
+        g = 2 * r * (us[k] - ug) + B.T @ lam
+        D[a] += (1 - c) * g
+        D[b] += c * g
+        lam = 2 * q * (X[k] - xg) + A.T @ lam
+    return D.reshape(p * m, N), J
