@@ -567,15 +567,6 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
     if (NT > (sizeof(T) == 8 ? 3 : 4) || UT > NT || UT > (NT == 4 || sizeof(T) == 8 ? 2 : 3) ||
         (int64_t)P.Tn * P.p > (1 << 30))
         return hipSuccess;
-    // A tile's step takes 4 NT MFMAs whatever the number of candidates; the
-    // per-candidate kernel holds 1024 (n <= 16) or 512 candidates at once and
-    // up to there takes the time of one.  With few candidates it stays the
-    // faster one where the MFMA chain is long (50 steps, us per call, that
-    // kernel / here): FP32 n = 28 49 / 35, n = 42 68 / 64, n = 60 69 / 79 at
-    // 64 candidates and 142 / 80 at 1024; FP64 n = 14 42 / 43 at 64 and
-    // 128 / 44 at 2048, five Adam steps on 64 142 / 191, n = 28 61 / 75 at 64
-    // and 124 / 77 at 1024.
-    if ((sizeof(T) == 8 || NT == 4) && ncand <= (NT == 1 ? 1024 : 512)) return hipSuccess;
     const int64_t tiles = (ncand + 15) / 16;
     auto bytes = [&](const LinAdjPlan &g) { return g.total * sizeof(T); };
     LinAdjPlan G = lin_adj_layout(NT, UT, P.Tn, P.p, steps > 0, P.Tn, true);
@@ -587,6 +578,29 @@ hipError_t launch_adjoint_linear_t(const ProbView<T> &P, const T *x0, const T *k
         if (bytes(B) <= MAX_GRAD_LDS) G = B;
     }
     if (bytes(G) > MAX_GRAD_LDS) return hipSuccess;
+    // Few candidates: up to the number that the per-candidate kernel holds at
+    // once (by its registers, 4, 2 or 1 workgroups per CU, and its LDS) it takes
+    // the time of one, about 2 T + sqrt(T) steps.  A tile's steps are shorter in
+    // FP32 up to 48 states, but it starts up longer and takes 3 T of them when its
+    // states do not fit.  us per call, that kernel / here, 32 to 1024 candidates:
+    //  FP32 n = 14, gradient: T = 10 13 / 14, T = 20 21 / 19, T = 100 75 / 61, in
+    //   blocks T = 150 108 / 120; three Adam steps: T = 20 59 / 61, T = 35 94 / 89
+    //  FP32 n = 28: T = 20 25 / 23, T = 50 49 / 43, in blocks T = 75 69 / 83;
+    //   three Adam steps T = 20 70 / 74, T = 50 150 / 144, in blocks T = 75 218 / 272
+    //  FP32 n = 42: T = 35 51 / 46, in blocks T = 50 68 / 83
+    //  FP32 n = 60: T = 20 34 / 39; FP64 n = 14: T = 50 43 / 48, in blocks T = 75
+    //   61 / 95; FP64 n = 28: T = 20 30 / 33, in blocks T = 50 62 / 96
+    //  FP64 n = 42 (that kernel spills): T = 20 81 / 58
+    //  a knot per step or two, FP32 n = 18, T = p = 50: 54 / 59
+    // Above that number it takes a multiple of its time (FP32 n = 42, T = 100: 128
+    // at 512 candidates, 254 at 768, 159 here).
+    const size_t other = grad_smem_bytes(EMPC_LINEAR, P.n, P.m, P.Tn, P.p, sizeof(T));
+    const int64_t by_regs = sizeof(T) == 4 ? (P.n <= 32 ? 4 : 2) : (P.n <= 16 ? 4 : P.n <= 32 ? 2 : 1);
+    const int64_t held = 256 * std::min<int64_t>(by_regs, MAX_GRAD_LDS / other);
+    const bool shorter = sizeof(T) == 8 ? NT > 2
+                                        : NT < 4 && G.full && 3 * P.p <= P.Tn &&
+                                              P.Tn >= (steps > 0 ? 28 : 16);
+    if (ncand <= held && !shorter) return hipSuccess;
     *taken = true;
     auto go = [&](auto kernel) {
         if (bytes(G) > 65536) {
