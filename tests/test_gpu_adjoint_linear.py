@@ -35,7 +35,7 @@ def case(n, m, T, p, ncand, dtype, box=False, seed=0, x0_scale=0.5):
     return prob, x0, knots
 
 
-def check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype, step_charge=False):
+def check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype):
     """FP64: 1e-9 of a column's largest entry (gradient), 1e-10 (cost); FP32:
     2e-3 and 1e-4, the rounding of T dependent steps."""
     dp, K = E.DeviceProblem(prob, dtype), dev(knots, dtype)
@@ -169,3 +169,39 @@ def grad_long(prob, x0, knots):
         D[b] += c * g
         lam = 2 * q * (X[k] - xg) + A.T @ lam
     return D.reshape(p * m, N), J
+
+
+# (states, inputs, horizon, knots, candidates, dtype): every instance of the
+# matrix-core kernel, with every state kept in LDS and in recomputed blocks,
+# ragged tiles of candidates, one knot, two steps per knot, a knot per step.  Few
+# candidates are enough where the kernel is chosen for its shorter steps; the
+# other cases have more than the per-candidate kernel holds at once.
+KEPT = [
+    (14, 5, 40, 4, 33, F32), (28, 14, 40, 6, 47, F32), (28, 28, 32, 5, 20, F32),
+    (42, 10, 30, 3, 31, F32), (48, 20, 28, 2, 16, F32), (40, 40, 28, 4, 20, F32),
+    (64, 16, 12, 12, 513, F32), (50, 20, 12, 1, 514, F32), (15, 7, 25, 25, 1031, F32),
+    (16, 16, 20, 4, 1040, F64), (17, 5, 12, 6, 515, F64), (32, 32, 8, 3, 520, F64),
+    (33, 9, 10, 5, 9, F64), (48, 20, 8, 2, 16, F64),
+]
+BLOCKS = [
+    (12, 4, 150, 7, 1030, F32), (30, 9, 80, 5, 1041, F32), (20, 20, 80, 9, 1030, F32),
+    (33, 16, 60, 6, 530, F32), (44, 31, 60, 4, 520, F32), (36, 36, 60, 3, 517, F32),
+    (64, 16, 60, 5, 530, F32), (64, 32, 60, 3, 529, F32),
+    (11, 3, 90, 9, 1025, F64), (28, 14, 60, 5, 530, F64), (32, 17, 40, 3, 514, F64),
+    (48, 16, 30, 3, 40, F64), (40, 32, 30, 3, 33, F64),
+]
+# the per-candidate kernel: more input than state tiles, FP64 above 48 states or
+# 32 inputs, few candidates where its step is the shorter one
+PER_CANDIDATE = [
+    (5, 20, 10, 3, 7, F64), (64, 40, 11, 11, 600, F32), (60, 12, 9, 2, 700, F64),
+    (40, 36, 9, 3, 20, F64), (14, 7, 30, 30, 20, F32), (28, 14, 90, 4, 24, F32),
+    (20, 4, 25, 2, 40, F64),
+]
+
+
+@pytest.mark.parametrize("box", [False, True])
+@pytest.mark.parametrize("n,m,T,p,ncand,dtype", KEPT + BLOCKS + PER_CANDIDATE)
+def test_every_instance(oracle_lib, E, n, m, T, p, ncand, dtype, box):
+    prob, x0, knots = case(n, m, T, p, ncand, dtype, box=box)
+    check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype)
+    check_refine(oracle_lib, E, prob, x0, knots, ncand, dtype)
