@@ -147,12 +147,12 @@ __global__ __launch_bounds__(64 * WPB) void batch_roll_chain_rows(const BatchSlo
 }
 
 // one workgroup per problem: problem items[blockIdx.x] (items NULL: blockIdx.x)
-template <typename T, typename K, int CACHE>
+template <typename T, typename K, int CACHE, bool BRIEF>
 __global__ __launch_bounds__(SEL_THREADS) void batch_select(const BatchSlot<T> *__restrict__ slots,
                                                             const int *__restrict__ items,
                                                             int64_t pop, int k, int g, int last) {
     const BatchSlot<T> &S = slots[items ? items[blockIdx.x] : (int)blockIdx.x];
-    select_body<T, K, CACHE, SEL_THREADS>(
+    select_body<T, K, CACHE, BRIEF, SEL_THREADS>(
         global_ptr(S.cost), pop, k, global_ptr(S.knots[g & 1]), pop, S.P.p * S.P.m, S.P.m,
         global_ptr(S.elite_idx), global_ptr(S.best_idx), last ? global_ptr(S.elite_rows) : nullptr,
         global_ptr(S.elite_cost), global_ptr(S.has_elites), nullptr,
@@ -291,7 +291,7 @@ __global__ __launch_bounds__(64, persist_waves<TIER>()) void batch_persist(Persi
         if (prev + 1 != (unsigned)A.units[e.x]) continue;
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
         __syncthreads();
-        select_body<float, uint32_t, CACHE, 64, 1>(
+        select_body<float, uint32_t, CACHE, false, 64, 1>(
             global_ptr(S.cost), A.pop, A.k, global_ptr(S.knots[A.g & 1]), A.pop, S.P.p * S.P.m,
             S.P.m, global_ptr(S.elite_idx), global_ptr(S.best_idx),
             A.last ? global_ptr(S.elite_rows) : nullptr, global_ptr(S.elite_cost),
@@ -575,15 +575,19 @@ void launch_batch_select(const empc_batch *b, const int *items, int count, int g
                          hipStream_t st) {
     const int64_t pop = b->pop, per = (pop + SEL_THREADS - 1) / SEL_THREADS;
     const int k = b->ga.n_elite;
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(count), dim3(SEL_THREADS), 0, st, b->d_slots, items, pop, k,
+                           g, last);
+    };
+    const bool brief = select_brief(pop, k, SEL_THREADS, per <= 16 ? 16 : 0);
     if (per <= 4)
-        hipLaunchKernelGGL((batch_select<float, uint32_t, 4>), dim3(count), dim3(SEL_THREADS), 0, st,
-                           b->d_slots, items, pop, k, g, last);
+        brief ? go(batch_select<float, uint32_t, 4, true>)
+              : go(batch_select<float, uint32_t, 4, false>);
     else if (per <= 16)
-        hipLaunchKernelGGL((batch_select<float, uint32_t, 16>), dim3(count), dim3(SEL_THREADS), 0,
-                           st, b->d_slots, items, pop, k, g, last);
+        brief ? go(batch_select<float, uint32_t, 16, true>)
+              : go(batch_select<float, uint32_t, 16, false>);
     else
-        hipLaunchKernelGGL((batch_select<float, uint32_t, 0>), dim3(count), dim3(SEL_THREADS), 0, st,
-                           b->d_slots, items, pop, k, g, last);
+        go(batch_select<float, uint32_t, 0, false>);
 }
 
 // One generation's rollouts and selections in the persistent form: the

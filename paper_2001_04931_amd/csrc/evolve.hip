@@ -61,22 +61,29 @@ hipError_t launch_select(const ProbView<T> &P, const T *cost, const T *knots, in
     };
     // one wavefront's bitonic sort up to 256 candidates; 256 threads up to
     // 1024 candidates, else 1024 threads (measured at 4096: 7.1 against
-    // 9.2 us; at 16384: 11.6 against 21.4 us)
-    if (pop <= 256) {
+    // 9.2 us; at 16384: 11.6 against 21.4 us); with the short cut by its rule
+    auto with = [&](auto cache, auto nthr) {
+        constexpr int C = decltype(cache)::value, N = decltype(nthr)::value;
+        if constexpr (N == SEL_THREADS || C > 4)
+            if (select_brief(pop, k, N, C)) return go(select_kernel<T, K, C, N, true>, N);
+        go(select_kernel<T, K, C, N, false>, N);
+    };
+    using std::integral_constant;
+    const integral_constant<int, SEL_THREADS> small;
+    const integral_constant<int, 1024> large;
+    const int64_t per = (pop + 1023) / 1024;
+    if (pop <= 256)
         go(select_small_kernel<T, K>, 64);
-    } else if (pop <= 1024) {
-        go(select_kernel<T, K, 4, 256>, 256);
-    } else {
-        const int64_t per = (pop + 1023) / 1024;
-        if (per <= 4)
-            go(select_kernel<T, K, 4, 1024>, 1024);
-        else if (per <= 16)
-            go(select_kernel<T, K, 16, 1024>, 1024);
-        else if (per <= 64)
-            go(select_kernel<T, K, 64, 1024>, 1024);
-        else
-            go(select_kernel<T, K, 0, 1024>, 1024);
-    }
+    else if (pop <= 1024)
+        with(integral_constant<int, 4>(), small);
+    else if (per <= 4)
+        with(integral_constant<int, 4>(), large);
+    else if (per <= 16)
+        with(integral_constant<int, 16>(), large);
+    else if (per <= 64)
+        with(integral_constant<int, 64>(), large);
+    else
+        go(select_kernel<T, K, 0, 1024, false>, 1024);
     return hipGetLastError();
 }
 template hipError_t launch_select<float>(const ProbView<float> &, const float *, const float *,

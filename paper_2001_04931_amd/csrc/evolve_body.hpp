@@ -378,16 +378,39 @@ __device__ inline double key_value(uint64_t k) {
 // one and a half to three times k.  Those keys are compacted in index order
 // and ranked against each other by (key, index): ranks below k are the
 // parents.  If more keys than the workgroup has threads pass the threshold
-// (ties, k near the population), the radix passes follow.  Same total order,
-// same outputs.  Radix passes and short cut: one workgroup, 16384 costs 11.4
-// and 7.8 us; 512 workgroups of 256 threads and 1024 costs 41 and 37 us; but
-// 4096 costs in 1024 threads 6.3 and 7.2 us (four keys per thread make the
-// passes cheap, and the ranking is what is left), so that instance keeps the
-// passes alone.
+// (ties), the radix passes follow.  Same total order, same outputs.
 //
+// It is tried where it measured faster for every k on that side of the line,
+// in both key sizes (selection and population of one parameter, FP32, us with
+// the passes alone and with it):
+//  - 256 threads, up to 16 minima per wavefront: 1024 costs k = 32 11.5 / 8.3,
+//    k = 64 11.5 / 9.3; beyond, k = 96 11.9 / 13.6, k = 128 11.9 / 14.7 (the
+//    minima one after another, and from k = 129 mostly the passes after all);
+//  - 1024 threads and up to 16 costs each, k <= 96: 16384 costs k = 64 16.5 /
+//    11.8, k = 96 16.9 / 12.3; beyond, k = 128 17.0 / 17.8, k = 256 18.0 / 23.6
+//    (more than 256 candidates are ranked by two lanes each);
+//  - more costs per thread, every k: 65536 costs k = 256 44.1 / 34.2;
+//  - not 1024 threads of four costs: 4096 costs 6.3 and 7.2 us (the passes are
+//    cheap there, and the ranking is what is left).
+//
+// wavefronts whose threads all hold a key
+__host__ __device__ inline int brief_wavefronts(int64_t pop, int nthr) {
+    const int64_t per = (pop + nthr - 1) / nthr;
+    return (int)((pop + per - 1) / per) / 64;
+}
+// the rule above; cache: keys per thread that the instance keeps in registers
+inline bool select_brief(int64_t pop, int k, int nthr, int cache) {
+    const int full = brief_wavefronts(pop, nthr);
+    if (cache == 0 || full == 0 || (k + full - 1) / full > 64) return false;
+    if (nthr == SEL_THREADS) return (k + full - 1) / full <= 16;
+    return cache > 16 || (cache > 4 && k <= 96);
+}
+
+// BRIEF: with the short cut (an instance of its own: with it in the code, the
+// passes alone took 1 us longer for FP64 keys).
 // NREP: histogram replicas (a power of two <= 16); a one-wavefront selection
 // inside the persistent batched kernel takes 1 to keep its LDS small.
-template <typename T, typename K, int CACHE, int NTHR = SEL_THREADS, int NREP = HREP>
+template <typename T, typename K, int CACHE, bool BRIEF, int NTHR = SEL_THREADS, int NREP = HREP>
 __device__ __forceinline__ void select_body(
     const T *__restrict__ cost, int64_t pop, int k, const T *__restrict__ knots, int64_t ld,
     int pm, int m, int64_t *__restrict__ elite_idx_out, int64_t *__restrict__ best_idx_out,
@@ -401,14 +424,13 @@ __device__ __forceinline__ void select_body(
     __shared__ K s_ekey[Limits::MAX_ELITE];
     __shared__ int s_best_slot;
     // the short cut's candidates and ranks, in the histograms' memory
-    constexpr bool SHORT = CACHE > 0 && (NTHR == 256 || (NTHR > 256 && CACHE > 4));
-    static_assert(!SHORT || sizeof(hist) >= sizeof(K) * (NTHR + 64) + 8 * NTHR, "candidates fit");
+    static_assert(!BRIEF || sizeof(hist) >= sizeof(K) * (NTHR + 64) + 8 * NTHR, "candidates fit");
     K *s_ck = reinterpret_cast<K *>(&hist[0][0]);
     int *s_ci = reinterpret_cast<int *>(s_ck + NTHR + 64), *s_rank = s_ci + NTHR;
     __shared__ int wsum2[(NTHR / 64)];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    if constexpr (!SHORT)
+    if constexpr (!BRIEF)
         for (int b = tid; b < NREP * HSTRIDE; b += NTHR) hist[0][b] = 0;
 
     const int64_t per = (pop + NTHR - 1) / NTHR;
@@ -445,72 +467,68 @@ __device__ __forceinline__ void select_body(
         }
     };
     bool ranked = false;  // the short cut found the parents (uniform)
-    if constexpr (SHORT) {
+    if constexpr (BRIEF) {
         constexpr int NW = NTHR / 64;
-        const int nact = (int)((pop + per - 1) / per);  // threads that hold a key
-        const int full = nact / 64;                     // wavefronts whose threads all do
-        const int r = full > 0 ? (k + full - 1) / full : 65;
-        if (r <= 64) {
-            K mn = ~(K)0;
-            for_each_key([&](int64_t, K key) { mn = key < mn ? key : mn; });
-            K tw = 0;
-            for (int taken = 0; taken < r;) {  // uniform; equal minima leave together
-                tw = key_min(mn);
-                const unsigned long long hit = __ballot(mn == tw);
-                taken += __popcll(hit);
-                if (mn == tw) mn = ~(K)0;
-            }
-            if (lane == 0) s_lo[wave] = wave < full ? tw : (K)0;
+        const int full = brief_wavefronts(pop, NTHR), rounds = (k + full - 1) / full;
+        K mn = ~(K)0;
+        for_each_key([&](int64_t, K key) { mn = key < mn ? key : mn; });
+        K tw = 0;
+        for (int taken = 0; taken < rounds;) {  // uniform; equal minima leave together
+            tw = key_min(mn);
+            const unsigned long long hit = __ballot(mn == tw);
+            taken += __popcll(hit);
+            if (mn == tw) mn = ~(K)0;
+        }
+        if (lane == 0) s_lo[wave] = wave < full ? tw : (K)0;
+        __syncthreads();
+        K thr = s_lo[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w) thr = s_lo[w] > thr ? s_lo[w] : thr;
+        int mine = 0, total;
+        for_each_key([&](int64_t, K key) { mine += key <= thr ? 1 : 0; });
+        int pos = block_excl_scan<NW>(mine, wsum, &total);
+        if (total <= NTHR) {  // uniform
+            for_each_key([&](int64_t q, K key) {
+                if (key <= thr) {
+                    s_ck[pos] = key;
+                    s_ci[pos] = (int)(i0 + q);
+                    ++pos;
+                }
+            });
+            if (tid < 64) s_ck[total + tid] = ~(K)0;  // whole groups of four below
             __syncthreads();
-            K thr = s_lo[0];
-#pragma unroll
-            for (int w = 1; w < NW; ++w) thr = s_lo[w] > thr ? s_lo[w] : thr;
-            int mine = 0, total;
-            for_each_key([&](int64_t, K key) { mine += key <= thr ? 1 : 0; });
-            int pos = block_excl_scan<NW>(mine, wsum, &total);
-            if (total <= NTHR) {  // uniform
-                for_each_key([&](int64_t q, K key) {
-                    if (key <= thr) {
-                        s_ck[pos] = key;
-                        s_ci[pos] = (int)(i0 + q);
-                        ++pos;
-                    }
-                });
-                if (tid < 64) s_ck[total + tid] = ~(K)0;  // whole groups of four below
-                __syncthreads();
-                // rank of candidate c, counted by L lanes, four keys at a time
-                int sh = 0;
-                while (sh < 4 && (total << (sh + 1)) <= NTHR) ++sh;
-                const int L = 1 << sh, c = tid >> sh;
-                int rank = 0;
-                if (c < total) {
-                    typedef K k4 __attribute__((ext_vector_type(4)));
-                    const K key = s_ck[c];
+            // rank of candidate c, counted by L lanes, four keys at a time
+            int sh = 0;
+            while (sh < 4 && (total << (sh + 1)) <= NTHR) ++sh;
+            const int L = 1 << sh, c = tid >> sh;
+            int rank = 0;
+            if (c < total) {
+                typedef K k4 __attribute__((ext_vector_type(4)));
+                const K key = s_ck[c];
 #pragma unroll 2
-                    for (int j = 4 * (tid & (L - 1)); j < total; j += 4 * L) {
-                        const k4 o = *reinterpret_cast<const k4 *>(s_ck + j);
+                for (int j = 4 * (tid & (L - 1)); j < total; j += 4 * L) {
+                    const k4 o = *reinterpret_cast<const k4 *>(s_ck + j);
 #pragma unroll
-                        for (int q = 0; q < 4; ++q)
-                            rank += (o[q] < key || (o[q] == key && j + q < c)) ? 1 : 0;
-                    }
+                    for (int q = 0; q < 4; ++q)
+                        rank += (o[q] < key || (o[q] == key && j + q < c)) ? 1 : 0;
                 }
-                for (int q = 1; q < L; q <<= 1) rank += __shfl_xor(rank, q, 64);
-                if (c < total && (tid & (L - 1)) == 0) s_rank[c] = rank;
-                __syncthreads();
-                const bool in = tid < total && s_rank[tid] < k;
-                int kk;
-                const int slot = block_excl_scan<NW>(in ? 1 : 0, wsum2, &kk);
-                if (in) {
-                    s_elite[slot] = s_ci[tid];
-                    s_ekey[slot] = s_ck[tid];
-                    if (s_rank[tid] == 0) s_best_slot = slot;
-                }
-                ranked = true;
             }
+            for (int q = 1; q < L; q <<= 1) rank += __shfl_xor(rank, q, 64);
+            if (c < total && (tid & (L - 1)) == 0) s_rank[c] = rank;
+            __syncthreads();
+            const bool in = tid < total && s_rank[tid] < k;
+            int kk;
+            const int slot = block_excl_scan<NW>(in ? 1 : 0, wsum2, &kk);
+            if (in) {
+                s_elite[slot] = s_ci[tid];
+                s_ekey[slot] = s_ck[tid];
+                if (s_rank[tid] == 0) s_best_slot = slot;
+            }
+            ranked = true;
         }
     }
     if (!ranked) {
-    if constexpr (SHORT) {
+    if constexpr (BRIEF) {
         __syncthreads();  // s_lo is written again; the candidates' memory is free
         for (int b = tid; b < NREP * HSTRIDE; b += NTHR) hist[0][b] = 0;
     }
@@ -771,13 +789,13 @@ __global__ __launch_bounds__(64) void select_small_kernel(
         for (int i = lane; i < m; i += 64) u_star[i] = knots[(int64_t)i * ld + s_elite[bslot]];
 }
 
-template <typename T, typename K, int CACHE, int NTHR>
+template <typename T, typename K, int CACHE, int NTHR, bool BRIEF>
 __global__ __launch_bounds__(NTHR) void select_kernel(
     const T *__restrict__ cost, int64_t pop, int k, const T *__restrict__ knots, int64_t ld,
     int pm, int m, int64_t *__restrict__ elite_idx_out, int64_t *__restrict__ best_idx_out,
     T *__restrict__ elite_rows, T *__restrict__ elite_cost, int *__restrict__ has_elites,
     int *__restrict__ best_slot_out, T *__restrict__ u_star, T *__restrict__ best_cost) {
-    select_body<T, K, CACHE, NTHR>(cost, pop, k, knots, ld, pm, m, elite_idx_out, best_idx_out,
+    select_body<T, K, CACHE, BRIEF, NTHR>(cost, pop, k, knots, ld, pm, m, elite_idx_out, best_idx_out,
                                    elite_rows, elite_cost, has_elites, best_slot_out, u_star,
                                    best_cost);
 }
