@@ -197,6 +197,9 @@ __device__ __forceinline__ void population_tile(
     // d U_{a+1} for knot a < p-1 (d = (p-1)/(T-1), the knot spacing in steps
     // inverted)
     const T d = P.p > 1 ? (T)(P.p - 1) / (T)(P.Tn - 1) : (T)0;
+    // FP64 normals are some hundred instructions a pair: a pair that no lane
+    // needs (past the last parameter, parents' slots) is not drawn
+    constexpr bool WIDE = sizeof(T) == 8;
     for (int rg = 0; rg < R; ++rg) {
         const int j0 = jt + 16 * rg + 4 * w;
         if (j0 >= pm) break;
@@ -226,13 +229,15 @@ __device__ __forceinline__ void population_tile(
         }
         uint32_t f[4];
 #pragma unroll
-        for (int r = 0; r < 4; ++r)
+        for (int r = 0; r < 4; ++r) {
             f[r] = (m <= 32 ? fw.x : word(fw, ii[r] / 32)) >> (ii[r] % 32) & 1u;
+            if (WIDE && (j0 + r >= pm || elite_slot)) f[r] = 0;
+        }
         T z[4] = {0, 0, 0, 0};
         if (f[0] | f[1] | f[2] | f[3]) {
             const U4 wn = ga_draw(gs, slot, gen, tick, 0, (uint32_t)(gs.NB + j0 / 4));
-            box_muller<T>(wn.x, wn.y, z[0], z[1]);
-            box_muller<T>(wn.z, wn.w, z[2], z[3]);
+            if (!WIDE || (f[0] | f[1])) box_muller<T>(wn.x, wn.y, z[0], z[1]);
+            if (!WIDE || (f[2] | f[3])) box_muller<T>(wn.z, wn.w, z[2], z[3]);
         }
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
