@@ -22,7 +22,7 @@ namespace empc {
 // One workgroup per (problem, population tile) that holds parameters: the
 // map lists them problem after problem, so problems with fewer parameters
 // take fewer workgroups (no workgroups that would only exit).
-template <typename T, typename OFF>
+template <typename T>
 __global__ __launch_bounds__(POP_THREADS) void batch_population(const BatchSlot<T> *__restrict__ slots,
                                                         const int2 *__restrict__ popmap,
                                                         int64_t pop, int k, int elitism, T sigma,
@@ -51,7 +51,7 @@ __global__ __launch_bounds__(POP_THREADS) void batch_population(const BatchSlot<
     var.sigma_min = sigma_min;
     var.sigma_dist = sigma_dist;
     var.shift = first ? shift : 0;
-    population_tile<T, OFF>(P, gs, pop, k, elitism, sigma,
+    population_tile<T>(P, gs, pop, k, elitism, sigma,
                        first ? nullptr : global_ptr(S.knots[(g + 1) & 1]), pop,
                        first ? nullptr : global_ptr(S.elite_idx),
                        first ? global_ptr(S.elite_rows) : nullptr, cold,
@@ -541,16 +541,10 @@ void assign_streams(empc_batch *b, int ns) {
 void launch_batch_population(empc_batch *b, int g, unsigned *counters, int ncounters,
                              hipStream_t s) {
     const empc_ga &G = b->ga;
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)b->pop_wgs), dim3(POP_THREADS), 0, s, b->d_slots,
-                           b->d_popmap, b->pop, G.n_elite, G.elitism, (float)G.sigma,
-                           (uint32_t)G.seed, g, (const uint32_t *)b->d_tick, G.shift,
-                           (float)G.sigma_min, (float)G.sigma_dist, b->pop_r, counters, ncounters);
-    };
-    if (b->pop <= POP_NARROW<float>)
-        go(batch_population<float, uint32_t>);
-    else
-        go(batch_population<float, uint64_t>);
+    hipLaunchKernelGGL(batch_population<float>, dim3((unsigned)b->pop_wgs), dim3(POP_THREADS), 0, s,
+                       b->d_slots, b->d_popmap, b->pop, G.n_elite, G.elitism, (float)G.sigma,
+                       (uint32_t)G.seed, g, (const uint32_t *)b->d_tick, G.shift,
+                       (float)G.sigma_min, (float)G.sigma_dist, b->pop_r, counters, ncounters);
 }
 
 // The rollouts of one generation: fork the side streams from s, each class

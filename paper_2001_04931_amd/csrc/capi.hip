@@ -102,7 +102,7 @@ empc_status validate_grad(const empc_problem *P) {
 
 empc_status validate_ga(const empc_ga *G) {
     if (!G) return fail(EMPC_EINVAL, "ga is NULL");
-    if (G->pop < 1 || G->pop > (1 << 24)) return fail(EMPC_EINVAL, "pop=%d outside [1, 2^24]", G->pop);
+    if (G->pop < 1 || G->pop > Limits::MAX_POP) return fail(EMPC_EINVAL, "pop=%d outside [1, 2^24]", G->pop);
     if (G->n_elite < 1 || G->n_elite > G->pop)
         return fail(EMPC_EINVAL, "n_elite=%d outside [1, pop=%d]", G->n_elite, G->pop);
     if (G->n_elite > Limits::MAX_ELITE)

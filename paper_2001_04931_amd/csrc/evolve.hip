@@ -1,7 +1,5 @@
 // Single-problem evolutionary step launchers: next population and parent
 // selection (bodies in evolve_body.hpp).
-#include <algorithm>
-
 #include "evolve_body.hpp"
 
 namespace empc {
@@ -23,18 +21,10 @@ hipError_t launch_population(const ProbView<T> &P, const empc_ga &ga, const T *k
                       ? R_override
                       : (wgs1 >= 4096 ? 4 : wgs1 >= 2048 ? 2 : 1);
     const int64_t blocks = pop_tiles_s(ga.pop) * pop_tiles_g(pm, R);
-    // elite_idx names candidates below ld_in, the children are below ga.pop
-    const int64_t reach = elite_rows || cold_mode == 1 ? ga.pop : std::max<int64_t>(ga.pop, ld_in);
-    auto go = [&](auto kernel) {
-        hipLaunchKernelGGL(kernel, dim3((unsigned)blocks), dim3(POP_THREADS), 0, s, P, gs,
-                           (int64_t)ga.pop, ga.n_elite, ga.elitism, (T)ga.sigma, knots_in, ld_in,
-                           elite_idx, elite_rows, has_elites, cold_mode, knots_out, ld_out, tick,
-                           gen, var, R);
-    };
-    if (reach <= POP_NARROW<T>)
-        go(population_kernel<T, uint32_t>);
-    else
-        go(population_kernel<T, uint64_t>);
+    hipLaunchKernelGGL(population_kernel<T>, dim3((unsigned)blocks), dim3(POP_THREADS), 0, s, P, gs,
+                       (int64_t)ga.pop, ga.n_elite, ga.elitism, (T)ga.sigma, knots_in, ld_in,
+                       elite_idx, elite_rows, has_elites, cold_mode, knots_out, ld_out, tick, gen,
+                       var, R);
     return hipGetLastError();
 }
 template hipError_t launch_population<float>(const ProbView<float> &, const empc_ga &,

@@ -75,13 +75,11 @@ __device__ __forceinline__ T mutate_clamp(T v, bool flag, T sigma, T z, T lo, T 
 constexpr int POP_SLOTS = 64;   // slots per workgroup, one per lane
 constexpr int POP_GROUPS = 4;   // groups of four parameters, one per wavefront
 constexpr int POP_THREADS = 64 * POP_GROUPS;
-// largest row (candidates) whose byte offsets fit 32 bits
-template <typename T>
-constexpr int64_t POP_NARROW = ((int64_t)1 << 32) / (int64_t)sizeof(T);
+// byte offsets within a row are 32 bits wide: children and parents both lie
+// below the largest population, whatever the rows' leading dimension
+static_assert(Limits::MAX_POP * sizeof(double) <= (uint64_t)1 << 32, "offsets fit 32 bits");
 
-// OFF: the type of a row's byte offsets, uint32_t below 4 GiB per row
-// (POP_NARROW), else uint64_t.
-template <typename T, typename OFF = uint32_t>
+template <typename T>
 __device__ __forceinline__ void population_tile(
     const ProbView<T> &P, const GaStreams &gs, int64_t pop, int k, int elitism, T sigma,
     const T *__restrict__ knots_in, int64_t ld_in, const int64_t *__restrict__ elite_idx,
@@ -171,26 +169,26 @@ __device__ __forceinline__ void population_tile(
     // the parents stay in slots 0 .. k-1: only the first tiles hold any
     const bool elite_tile = elitism && tile_s * POP_SLOTS < k;  // uniform
     const bool elite_slot = elite_tile && s < k;
-    OFF o1, o2;
+    uint32_t o1, o2;
     if (elite_rows) {
-        o1 = (OFF)s_par[lane][0];
-        o2 = (OFF)s_par[lane][1];
-        if (elite_slot) o1 = o2 = (OFF)s;
+        o1 = (uint32_t)s_par[lane][0];
+        o2 = (uint32_t)s_par[lane][1];
+        if (elite_slot) o1 = o2 = (uint32_t)s;
     } else {
-        o1 = (OFF)s_eidx[s_par[lane][0]];
-        o2 = (OFF)s_eidx[s_par[lane][1]];
-        if (elite_slot) o1 = o2 = (OFF)s_eidx[s];
+        o1 = (uint32_t)s_eidx[s_par[lane][0]];
+        o2 = (uint32_t)s_eidx[s_par[lane][1]];
+        if (elite_slot) o1 = o2 = (uint32_t)s_eidx[s];
     }
-    o1 *= (OFF)sizeof(T);
-    o2 *= (OFF)sizeof(T);
+    o1 *= (uint32_t)sizeof(T);
+    o2 *= (uint32_t)sizeof(T);
     typedef uint32_t w4 __attribute__((ext_vector_type(4)));
     const w4 fw = *reinterpret_cast<const w4 *>(&s_flag[lane][0]);
     const w4 xw = *reinterpret_cast<const w4 *>(&s_xw[lane][0]);
     auto word = [](const w4 &v, int q) {  // q uniform
         return q == 0 ? v.x : (q == 1 ? v.y : (q == 2 ? v.z : v.w));
     };
-    const OFF os = (OFF)s * (OFF)sizeof(T);
-    auto at = [](const T *row, OFF off) {
+    const uint32_t os = (uint32_t)s * (uint32_t)sizeof(T);
+    auto at = [](const T *row, uint32_t off) {
         return *reinterpret_cast<const T *>(reinterpret_cast<const char *>(row) + off);
     };
     // with the shift, the carried input one control step later: (1-d) U_a +
@@ -221,7 +219,7 @@ __device__ __forceinline__ void population_tile(
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
             const int j = j0 + r < pm ? j0 + r : pm - 1;
-            const OFF o = (xb >> r) & 1u ? o2 : o1;
+            const uint32_t o = (xb >> r) & 1u ? o2 : o1;
             pv[r] = at(base + (int64_t)j * step, o);
             if (var.shift) pn[r] = at(base + (int64_t)(ka[r] < P.p - 1 ? j + m : j) * step, o);
             lo[r] = P.umin[ii[r]];
@@ -258,7 +256,7 @@ __host__ __device__ inline int pop_tiles_g(int pm, int R = 1) {
     return ((pm + 3) / 4 + POP_GROUPS * R - 1) / (POP_GROUPS * R);
 }
 
-template <typename T, typename OFF>
+template <typename T>
 __global__ __launch_bounds__(POP_THREADS) void population_kernel(
     ProbView<T> P, GaStreams gs, int64_t pop, int k, int elitism, T sigma,
     const T *__restrict__ knots_in, int64_t ld_in, const int64_t *__restrict__ elite_idx,
@@ -267,7 +265,7 @@ __global__ __launch_bounds__(POP_THREADS) void population_kernel(
     int R) {
     const bool cold = cold_mode == 1 || (cold_mode == 2 && *has_elites == 0);
     const int64_t nts = pop_tiles_s(pop);
-    population_tile<T, OFF>(P, gs, pop, k, elitism, sigma, knots_in, ld_in, elite_idx, elite_rows, cold,
+    population_tile<T>(P, gs, pop, k, elitism, sigma, knots_in, ld_in, elite_idx, elite_rows, cold,
                        knots_out, ld_out, tick, gen, blockIdx.x % nts, (int)(blockIdx.x / nts),
                        var, R);
 }

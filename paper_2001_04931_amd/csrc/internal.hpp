@@ -241,6 +241,7 @@ struct Limits {
     static constexpr int MAX_M_LINEAR = 40;
     static constexpr int MAX_D_CHAIN = 40;
     static constexpr int MAX_ELITE = 256;
+    static constexpr int MAX_POP = 1 << 24;
 };
 constexpr int VALU_FULL_NMAX = 64;  // largest n with full weights
 constexpr int VALU_FULL_MMAX = 32;  // largest m with full weights
