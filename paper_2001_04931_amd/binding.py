@@ -149,12 +149,20 @@ def _ptr(t: Optional[torch.Tensor]):
     return t.data_ptr()
 
 
+# The handle of the current stream without a Stream object around it: the
+# smallest calls are bound by the binding.  torch keeps the accessor private:
+# where it is missing, the public call.
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+
+
 def _stream(stream=None):
-    # the handle itself, without a Stream object around it: the calls below
-    # take argument types, so plain integers become pointers there
-    if stream is None:
-        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
-    return stream.cuda_stream
+    # the handle itself: the calls below take argument types, so plain integers
+    # become pointers there
+    if stream is not None:
+        return stream.cuda_stream
+    if _raw_stream is not None:
+        return _raw_stream(torch.cuda.current_device())
+    return torch.cuda.current_stream().cuda_stream
 
 
 def _cprob(prob):
