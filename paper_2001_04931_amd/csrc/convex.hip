@@ -173,7 +173,11 @@ __global__ __launch_bounds__(FORM_THREADS) void qp_form_kernel(
         const double *Si = S + min(i0 + c, pm - 1), *Sj = S + min(j0 + c, pm - 1);
         v4d acc = {0, 0, 0, 0};
         int kr = kb + g, k = kr / n, r = kr % n;
-        constexpr int U = 22;  // MFMAs per batch of loads in flight
+        // MFMAs per batch of loads in flight.  A slice ends within a batch, whose
+        // rest multiplies zeros: 8, 12, 16, 22 per batch, us: 400 rows of 40
+        // parameters 8.4, 9.5, 8.6, 9.9; 1400 of 140 16.8, 16.3, 16.3, 15.7;
+        // 1500 of 150 16.8, 16.6, 16.3, 19.6.
+        constexpr int U = 8;
         for (int k0 = kb; k0 < ke; k0 += 4 * U) {
             double a[U], b[U];
 #pragma unroll
@@ -767,21 +771,32 @@ __global__ __launch_bounds__(BOX_THREADS) void qp_box_small_kernel(
                 PT[(int64_t)(c0 + k) * pm + r] = H[k * (pm + 1) + r];
         __syncthreads();
     }
-    // (P v)_i for v in LDS, 28 loads in flight
+    // (P v)_i for v in LDS.  Twenty loads in flight, the rest one more batch of
+    // them with clamped rows: a thread waits for memory once per batch, and a
+    // longer batch does more beyond the last row.  16, 20, 24, 32 loads, us per
+    // solve: 49 parameters 39, 40, 39, 42; 100 75, 72, 75, 78; 140 124, 121,
+    // 125, 129; 160 121, 120, 124, 124.
     auto pdot = [&](const double *v) {
         double s = 0.0;
         if (mine) {
             const double *col = PT + i;
             int j = 0;
-            for (; j + 28 <= pm; j += 28) {
-                double t[28];
+            constexpr int U = 20;
+            for (; j + U <= pm; j += U) {
+                double t[U];
 #pragma unroll
-                for (int u = 0; u < 28; ++u) t[u] = col[(int64_t)(j + u) * pm];
+                for (int u = 0; u < U; ++u) t[u] = col[(int64_t)(j + u) * pm];
 #pragma unroll
-                for (int u = 0; u < 28; ++u) s += t[u] * v[j + u];
+                for (int u = 0; u < U; ++u) s += t[u] * v[j + u];
             }
-#pragma unroll 4
-            for (; j < pm; ++j) s += col[(int64_t)j * pm] * v[j];
+            if (j < pm) {
+                double t[U];
+#pragma unroll
+                for (int u = 0; u < U; ++u) t[u] = col[(int64_t)min(j + u, pm - 1) * pm];
+#pragma unroll
+                for (int u = 0; u < U; ++u)
+                    if (j + u < pm) s += t[u] * v[j + u];
+            }
         }
         return s;
     };
