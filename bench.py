@@ -56,11 +56,11 @@ PEAK_FP32_VALU = 78.6e12   # MI355X FP32 vector peak without packed math, FLOP/s
 PEAK_FP64 = 78.6e12        # MI355X FP64 (vector and matrix), FLOP/s
 CSRC = os.path.join(ROOT, "paper_2001_04931_amd", "csrc")
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "rollout_linear_c2_traffic.md")
-ROLLOUT_SRCS = [os.path.join(CSRC, f) for f in ("rollout_linear.hpp", "internal.hpp")]
+ROLLOUT_SRCS = [os.path.join(CSRC, f) for f in ("rollout_linear.hpp", "mfma.hpp", "internal.hpp")]
 BATCH_TRAFFIC_FILE = os.path.join(ROOT, "profiles", "batch_tick_c5_traffic.md")
 BATCH_SRCS = [os.path.join(CSRC, f) for f in ("batched.hip", "rollout_linear.hpp",
                                                "rollout_chain.hpp", "evolve_body.hpp",
-                                               "rollout_valu.hpp", "internal.hpp")]
+                                               "rollout_valu.hpp", "mfma.hpp", "internal.hpp")]
 
 
 # ---------------------------------------------------------------------------

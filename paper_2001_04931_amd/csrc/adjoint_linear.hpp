@@ -30,7 +30,7 @@
 #include <algorithm>
 
 #include "internal.hpp"
-#include "rollout_linear.hpp"
+#include "mfma.hpp"
 
 namespace empc {
 

@@ -21,6 +21,7 @@
 #include <math.h>
 
 #include "internal.hpp"
+#include "mfma.hpp"
 
 namespace empc {
 

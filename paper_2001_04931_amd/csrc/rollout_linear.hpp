@@ -28,36 +28,11 @@
 #include <math.h>
 
 #include "internal.hpp"
+#include "mfma.hpp"
+#include "rollout_full.hpp"
 #include "rollout_valu.hpp"
 
 namespace empc {
-
-// s_waitcnt operand for gfx9: vmcnt = 0, expcnt and lgkmcnt left at their
-// maxima (no wait)
-constexpr int VMCNT0 = 0x0F70;
-
-template <typename T>
-struct Mfma;
-template <>
-struct Mfma<float> {
-    typedef float v4 __attribute__((ext_vector_type(4)));
-    __device__ static inline v4 op(float a, float b, v4 c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    // state held by register v of lane group g, and the state whose row the
-    // A operand of lane c (output row c) carries
-    __device__ static constexpr int row(int g, int v) { return g + 4 * v; }
-    __device__ static constexpr int mstate(int c) { return (c >> 2) + 4 * (c & 3); }
-};
-template <>
-struct Mfma<double> {
-    typedef double v4 __attribute__((ext_vector_type(4)));
-    __device__ static inline v4 op(double a, double b, v4 c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    __device__ static constexpr int row(int g, int v) { return g + 4 * v; }
-    __device__ static constexpr int mstate(int c) { return c; }
-};
 
 // NT = ceil(n / 16) M-tiles, NU = ceil(m / 4) input K-slices; HAS_XG: the
 // problem has a state goal (else (x - g) is x itself).
@@ -345,14 +320,7 @@ __global__ __launch_bounds__(64 * WPB) void roll_linear_mfma(ProbView<T> P,
 // Registers are indexed by slot i = 0..NT-1 holding M-tile (w + i) mod NT, so
 // slot 0 is always the wavefront's own tile and every register index stays a
 // compile-time constant; A_d's columns are loaded in the same rotated order.
-__device__ inline void lds_barrier() {
-    // orders LDS accesses only: outstanding global loads (knot prefetches)
-    // are not waited for
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-    __builtin_amdgcn_s_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-}
-
+//
 // One workgroup of 64 NT threads: candidates 16*tile .. 16*tile+15 (tile
 // must hold at least one candidate: the whole workgroup takes part in every
 // barrier).
@@ -580,10 +548,6 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_split(ProbView<T> P,
     linear_tile_split<T, NT, NU, HAS_XG, BOX>(P, x0, knots, ld, ncand, cost,
                                               xcd_swizzle(blockIdx.x, gridDim.x));
 }
-
-}  // namespace empc
-#include "rollout_full.hpp"
-namespace empc {
 
 // Launch through hipExtLaunchKernelGGL when timing events are given: the
 // events are stamped by the kernel's own dispatch, with no extra stream
