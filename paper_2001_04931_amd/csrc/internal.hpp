@@ -48,7 +48,8 @@ inline ProbView<T> view_of(const empc_problem &P) {
     return v;
 }
 
-// the problem has full weights (the vector-ALU rollout handles them)
+// the problem has full weights (rollout_full.hpp; the vector-ALU form takes
+// the small ones when tuned)
 template <typename T>
 __host__ __device__ inline bool full_weights(const ProbView<T> &P) {
     return P.Qm || P.Rm || P.Qfm;
