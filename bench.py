@@ -278,6 +278,17 @@ def kernel_roofline(prof, flop_launch, peak, name, bound="mfma", **extra):
 # ---------------------------------------------------------------------------
 # the batch (headline) and its other forms
 
+def compact(o):
+    """The result with every float at seven significant digits: no figure here
+    is known to more, and with all seventeen the one line of output outgrows
+    what readers of it keep (20000 characters were too many)."""
+    if isinstance(o, dict):
+        return {k: compact(v) for k, v in o.items()}
+    if isinstance(o, (list, tuple)):
+        return [compact(v) for v in o]
+    return float("%.7g" % o) if isinstance(o, float) else o
+
+
 def c5_problems(W):
     probs, ga = W.config_c5(512, 0)
     return [p.cast(np.float32) for p in probs], ga
@@ -840,10 +851,10 @@ def main():
     with_cpu = not args.no_cpu_baseline
     if args.only == "c5":
         r, _, _ = c5_workload(E, W, args.steps, args.warmup, with_cpu)
-        print(json.dumps(r), flush=True)
+        print(json.dumps(compact(r)), flush=True)
         return
     if args.only:
-        print(json.dumps(other_workloads(E, W, (args.only,), with_cpu)), flush=True)
+        print(json.dumps(compact(other_workloads(E, W, (args.only,), with_cpu))), flush=True)
         return
     t0 = time.perf_counter()
     r, probs, ga = c5_workload(E, W, args.steps, args.warmup, with_cpu)
@@ -880,7 +891,7 @@ def main():
         out["cpu_baseline_all_cores"] = r["cpu_baseline_all_cores"]
     if not args.no_workloads:
         out["workloads"] = other_workloads(E, W, WORKLOADS, with_cpu, (probs, ga))
-    print(json.dumps(out), flush=True)
+    print(json.dumps(compact(out)), flush=True)
 
 
 if __name__ == "__main__":
