@@ -21,9 +21,10 @@
 // per candidate on the vector ALUs, 44 us here (65536: 3.1 ms and 0.47 ms); 64
 // candidates with five Adam steps: 235 and 220 us.
 // Products with B_d per knot instead of per step, blended (41 us, 202 us), lost
-// accuracy: see drive.  Errors against 64 bits are those of the per-candidate
-// kernel or less (FP32 gradient, rms over sizes and horizons: 0.80 to 0.93 of
-// them; cost 0.88 to 0.95).
+// accuracy: see drive.  Errors against 64 bits, relative to the per-candidate
+// kernel's (FP32, rms over horizons of 20 to 200): gradient 0.89 to 1.00 and cost
+// 0.92 to 0.98 for random models of 14 to 60 states, 0.52 to 0.69 and 0.60 to 0.79
+// for spring chains of 2 to 30 DoF (see the diagonal below).
 #pragma once
 #include <math.h>
 
@@ -38,7 +39,7 @@ namespace empc {
 struct LinAdjPlan {
     int full;          // every state kept
     int S, nblk;       // steps per block and blocks (full: one block)
-    size_t oX, oL, oD, oR, oC, oU, oM1, oM2, oG, total;
+    size_t oX, oL, oD, oR, oQ, oC, oU, oM1, oM2, oG, total;
 };
 inline LinAdjPlan lin_adj_layout(int NT, int UT, int T, int p, bool refine, int S, bool full) {
     LinAdjPlan g;
@@ -56,6 +57,7 @@ inline LinAdjPlan lin_adj_layout(int NT, int UT, int T, int p, bool refine, int 
     g.oM2 = o; o += refine ? kn : 0;
     g.oG = o; o += refine ? kn : 0;
     g.oR = o; o += (size_t)(NT + UT) * 16;
+    g.oQ = o; o += (size_t)NT * 16;
     g.oC = o; o += (size_t)T + 1;
     g.total = o;
     return g;
@@ -361,37 +363,43 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
     }
 
     // A state wavefront.  A operands by slot i (M-tile t =
-    // (w + i) mod NT): rows of A_d and of A_d^T
+    // (w + i) mod NT): rows of A_d and of A_d^T without the diagonal, which a
+    // product adds last: discretized dynamics are close to the identity, and
+    // every further term after the diagonal's rounds by the state's own size
+    // (21-DoF chain, 100 steps, FP32: error of the gradient 9.7e-7 with the
+    // diagonal in the sums, 4.8e-7 this way, 7.6e-7 in the per-candidate kernel).
     T aX[4 * NT], aT[4 * NT];
 #pragma unroll
     for (int i = 0; i < NT; ++i)
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const int row = 16 * w + arow, kk = 16 * ((w + i) % NT) + Mfma<T>::row(grp, v);
-            const bool in = row < n && kk < n;
+            const bool in = row < n && kk < n && row != kk;
             aX[4 * i + v] = in ? P.Ad[row * n + kk] : (T)0;
             aT[4 * i + v] = in ? P.Ad[kk * n + row] : (T)0;
         }
     // own rows: start state, goal, weights, box
-    v4 X0, Xg, Q, Qf, Lo, Hi, Qb;
+    v4 X0, Xg, Q, Lo, Hi, Qb, Diag;
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int row = 16 * w + Mfma<T>::row(grp, v);
         const bool in = row < n, bx = in && box;
         X0[v] = in ? x0[row] : (T)0;
+        Diag[v] = in ? P.Ad[row * n + row] : (T)0;
         Xg[v] = in && P.xg ? P.xg[row] : (T)0;
         Q[v] = in ? P.q[row] : (T)0;
-        Qf[v] = in && P.qf ? P.qf[row] : (T)0;
+        sm[G.oQ + row] = in && P.qf ? P.qf[row] : (T)0;
         Lo[v] = bx ? P.xlo[row] : (T)-1;
         Hi[v] = bx ? P.xhi[row] : (T)1;
         Qb[v] = bx ? P.qb[row] : (T)0;
     }
     // M V over all M-tiles of a vector V, this wavefront's rows of the
-    // matrix in `op` (by slot): V's own tile from registers, the others from
+    // matrix in `op` (by slot) and the diagonal, plus what `plus` adds to two of
+    // the four partial sums: V's own tile from registers, the others from
     // `at`, where every wavefront has stored its own before the call.  The
     // barrier sits between the own slices, as in the M-split rollout, and
     // `shadow`, vector work of no use to this product, behind them.
-    auto contract = [&](const T *op, v4 own, T *at, auto &&shadow)
+    auto contract = [&](const T *op, v4 own, T *at, auto &&shadow, auto &&plus)
                         __attribute__((always_inline)) {
         // four partial sums, added pairwise: the rounding of the per-candidate
         // kernel's dot products (with two the gradient's error is 1.3 times
@@ -415,26 +423,36 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
             for (int v = 0; v < 4; ++v)
                 acc[(v & 1) + 2 * (i & 1)] =
                     Mfma<T>::op(op[4 * i + v], o[i][v], acc[(v & 1) + 2 * (i & 1)]);
-        return (acc[0] + acc[1]) + (acc[2] + acc[3]);
+        v4 sum = (acc[0] + acc[1]) + plus(acc[2] + acc[3]);
+#pragma unroll
+        for (int v = 0; v < 4; ++v) sum[v] += Diag[v] * own[v];
+        return sum;
     };
     // States x_{k0+1} .. x_{k1} from X = x_{k0}, which every wavefront has
     // stored at `at`; to(k): where x_k goes; each(x_k, k): called in the shadow of
-    // the step that leaves x_k.  B_d u_k + w_d is added last: the sums of A_d x
-    // round by their own size.
+    // the step that leaves x_k.
     auto march = [&](int k0, int k1, v4 X, T *at, auto &&to, auto &&each)
                      __attribute__((always_inline)) {
         for (int k = k0; k < k1; ++k) {
             v4 Bu;
-            X = contract(aX, X, at, [&, X]() {
+            X = contract(
+                aX, X, at,
+                [&, X]() {
                     Bu = *tile(drive_at(k & 1), w);
                     each(X, k);
-                }) + Bu;
+                },
+                [](const v4 &sum) { return sum; });
+            X += Bu;
             at = to(k + 1);
             *tile(at, w) = X;
         }
         return X;
     };
-    v4 XT = X0;
+    // x_0 stays in its slot, which no pass overwrites; the terminal weights, of
+    // use once per pass, in LDS too
+    *tile(slot(0), w) = X0;
+    auto terminal = [&](int v) { return sm[G.oQ + 16 * w + Mfma<T>::row(grp, v)]; };
+    v4 XT;
     // cost of the knots in sU; leaves the states in LDS and x_T in XT
     auto forward = [&]() __attribute__((always_inline)) -> T {
         // sums over x_1 .. x_T: every step adds the state that it leaves, x_T
@@ -455,11 +473,11 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
                 }
             }
         };
-        *tile(slot(0), w) = X0;
+        const v4 Xs = *tile(slot(0), w);
         if (G.full) {
             T *at = slot(0);
             XT = march(
-                0, Tn, X0, at,
+                0, Tn, Xs, at,
                 // x_T is not read back: it goes into the ring of lambda, which is
                 // idle here (not into a state's slot: other wavefronts may still
                 // be reading the last step's, which for T = 1 is x_0's)
@@ -472,7 +490,7 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
             T *ring = slot(G.nblk + G.S), *chk = slot(0);
             int q = 0;
             XT = march(
-                0, Tn, X0, chk,
+                0, Tn, Xs, chk,
                 [&](int k) -> T * {
                     if (++q == G.S && k < Tn) {
                         q = 0;
@@ -488,7 +506,7 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
             const double e = XT[v] - Xg[v];
-            J += (double)Q[v] * S[v] + (double)Qf[v] * e * e;
+            J += (double)Q[v] * S[v] + (double)terminal(v) * e * e;
             if (box) J += (double)Qb[v] * Pn[v];
         }
         if (box && P.sb) {
@@ -508,7 +526,7 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
         v4 L;
 #pragma unroll
         for (int v = 0; v < 4; ++v) {
-            L[v] = (T)2 * (Q[v] + Qf[v]) * (XT[v] - Xg[v]);
+            L[v] = (T)2 * (Q[v] + terminal(v)) * (XT[v] - Xg[v]);
             if (box) L[v] += box_pen_grad(XT[v], Lo[v], Hi[v], Qb[v]);
         }
         int par = 0;
@@ -530,18 +548,22 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
                 *tile(at, w) = L;
                 if (k >= 1) {
                     v4 e, s = zero;
-                    L = contract(aT, L, at, [&]() {
-                        e = (T)2 * (X - Xg);
-                        if (box) {
+                    L = contract(
+                        aT, L, at,
+                        [&]() {
+                            e = (T)2 * (X - Xg);
+                            if (box) {
 #pragma unroll
-                            for (int v = 0; v < 4; ++v)
-                                s[v] = box_pen_grad(X[v], Lo[v], Hi[v], Qb[v]);
-                        }
-                        X = *tile(seg + (k > k0 ? k - 1 - k0 : 0) * (NT * 256), w);
-                    });
+                                for (int v = 0; v < 4; ++v)
+                                    s[v] = box_pen_grad(X[v], Lo[v], Hi[v], Qb[v]);
+                            }
+                            X = *tile(seg + (k > k0 ? k - 1 - k0 : 0) * (NT * 256), w);
+                        },
+                        [&](v4 sum) {
 #pragma unroll
-                    for (int v = 0; v < 4; ++v) L[v] += Q[v] * e[v];
-                    if (box) L += s;
+                            for (int v = 0; v < 4; ++v) sum[v] += Q[v] * e[v];
+                            return box ? sum + s : sum;
+                        });
                 } else {
                     lds_barrier();
                 }

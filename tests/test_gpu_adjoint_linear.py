@@ -205,3 +205,26 @@ def test_every_instance(oracle_lib, E, n, m, T, p, ncand, dtype, box):
     prob, x0, knots = case(n, m, T, p, ncand, dtype, box=box)
     check_grad(oracle_lib, E, prob, x0, knots, ncand, dtype)
     check_refine(oracle_lib, E, prob, x0, knots, ncand, dtype)
+
+
+@pytest.mark.parametrize("dtype,d,T", [(F32, 21, 100), (F32, 30, 60), (F64, 14, 60)])
+def test_no_less_exact_than_the_per_candidate_kernel(E, dtype, d, T):
+    """Spring chains, whose model is close to the identity: 64 candidates alone run
+    the per-candidate kernel (their horizon does not fit in LDS), the same 64 among
+    528 the matrix cores.  Against extended precision the second may be off by a
+    tenth more than the first, the spread of an rms over 64 candidates' worst
+    entries."""
+    npd = np.float32 if dtype == F32 else np.float64
+    prob = W.linear_chain(d, T, 5, seed=2).cast(npd)
+    x0 = W.draw_x0(prob.n, 1, scale=1.0).astype(npd).astype(np.float64)
+    knots = W.draw_knots(prob, 528, 4).astype(npd).astype(np.float64)
+    want, wcost = grad_long(prob, x0, knots[:, :64])
+    dp, rms = E.DeviceProblem(prob, dtype), []
+    for nc in (64, 528):
+        K = dev(knots[:, :nc], dtype)
+        dJ, cost = torch.empty_like(K), dev(np.zeros(nc), dtype)
+        E.empc_grad(dp, dev(x0, dtype), K, nc, nc, dJ, cost)
+        err = np.abs(dJ.cpu().numpy()[:, :64] - want).max(axis=0) / np.abs(want).max(axis=0)
+        cerr = cost.cpu().numpy()[:64] / wcost - 1
+        rms.append([np.sqrt(np.mean(e.astype(float) ** 2)) for e in (err, cerr)])
+    assert rms[1][0] <= 1.1 * rms[0][0] and rms[1][1] <= 1.1 * rms[0][1]
