@@ -6,8 +6,15 @@
 // M-split rollout (rollout_linear.hpp).  The weight product Q x_k is a second
 // contraction over the same B operands as A_d x_k: its 4 NT MFMAs per step
 // depend on nothing in the step, so they run while the new state's sums
-// finish and go through LDS.  The stage cost adds (x - g)^T (Q x - Q g) with
-// Q g precomputed (at x_T, Q (x - g)).  The input cost of a knot segment is closed form in
+// finish and go through LDS.  The stage cost is (x - g)^T Q (x - g): with one
+// M-tile the product takes x - g itself, with more it is Q x - Q g, Q g
+// precomputed; at x_T, Q (x - g) always.  The diagonal of A_d is left out of the
+// operands and added last, by one fused operation: near the identity the terms
+// after it would round by the state's own size (FP32, error of the cost
+// relative to the vector-ALU form, spring chains of 2 to 30 DoF: 0.65 to 1.18
+// with the diagonal in its K slice, 0.26 to 0.68 this way, for 2 to 7 % of the
+// time; states around a goal 100 units away 0.51 to 1.12, now 0.30 to 0.84).  The
+// input cost of a knot segment is closed form in
 // E_a = U_a - u_g and R E_a, one product per knot:
 //   S00 E_a^T R E_a + 2 S01 E_a^T R E_b + S11 E_b^T R E_b
 // with the sums of (1-c)^2, c (1-c), c^2 over the segment.  The terminal
@@ -16,7 +23,7 @@
 // The step's chain of MFMAs bounds it (8 NT of them, 32 cycles each in FP32).
 // On the vector ALUs, 16 lanes per candidate with A_d and Q read from LDS in
 // every step, the 7-DoF chain (4096 candidates, 50 steps, FP32) took 40 us;
-// here 16 us; 32 DoF 273 and 55 us; FP64 42 and 27, 362 and 94 us (2048).
+// here 17.4 us; 32 DoF 245 and 54 us; FP64 47 and 29, 322 and 93 us.
 #pragma once
 #include <math.h>
 
@@ -69,7 +76,7 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
         for (int v = 0; v < 4; ++v) {
             const int kk = 16 * ((w + i) % NT) + Mfma<T>::row(grp, v);
             const bool in = arow < n && kk < n;
-            aX[4 * i + v] = in ? P.Ad[arow * n + kk] : (T)0;
+            aX[4 * i + v] = in && arow != kk ? P.Ad[arow * n + kk] : (T)0;  // diagonal apart
             aQ[4 * i + v] = in ? q_at(arow, kk) : (T)0;
         }
 #pragma unroll
@@ -86,7 +93,7 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
                                           : (T)0;
         }
     }
-    v4 X, Wd, Xg, Lo, Hi, Pn = {0, 0, 0, 0}, Cn = {0, 0, 0, 0};
+    v4 X, Wd, Xg, Diag, Lo, Hi, Pn = {0, 0, 0, 0}, Cn = {0, 0, 0, 0};
 #pragma unroll
     for (int v = 0; v < 4; ++v) {
         const int row = 16 * w + Mfma<T>::row(grp, v);
@@ -94,6 +101,7 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
         X[v] = in ? x0[row] : (T)0;
         Wd[v] = in && P.wd ? P.wd[row] : (T)0;
         Xg[v] = in && P.xg ? P.xg[row] : (T)0;
+        Diag[v] = in ? P.Ad[row * n + row] : (T)0;
         Lo[v] = BOX && in ? P.xlo[row] : (T)-1;  // padding rows: around their zero state
         Hi[v] = BOX && in ? P.xhi[row] : (T)1;
     }
@@ -144,14 +152,14 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
     };
     // Q g, from the goal published like a state
     v4 V[NT], Qg;
-    {
+    if constexpr (NT > 1) {
         const v4 x = X;
         X = Xg;
-        if (NT > 1) xs[1][w][lane] = X;
+        xs[1][w][lane] = X;
         gather(1, V);
         Qg = contract(aQ, V, v4{0, 0, 0, 0});
         X = x;
-        if (NT > 1) xs[0][w][lane] = X;
+        xs[0][w][lane] = X;
     }
     v4 Va = response(Ka), Vb = response(Kb), REa[UW], REb[UW];
     r_times(Ka, REa);
@@ -178,14 +186,21 @@ __global__ __launch_bounds__(64 * NT) void roll_linear_full(ProbView<T> P,
             s11 += c * c;
             gather(buf, V);
             const v4 Xk = X;
-            X = contract(aX, V, Va + c * dV);
+            X = contract(aX, V, v4{0, 0, 0, 0}) + (Va + c * dV);
+#pragma unroll
+            for (int v = 0; v < LV; ++v) X[v] += Diag[v] * Xk[v];
             buf ^= 1;
             if (NT > 1) xs[buf][w][lane] = X;
             // stage cost of x_k (x_0 has none), beside the new state's way
-            const v4 QE = contract(aQ, V, -Qg);
+            const v4 E = Xk - Xg;
+            v4 QE;
+            if constexpr (NT == 1)
+                QE = contract(aQ, &E, v4{0, 0, 0, 0});
+            else
+                QE = contract(aQ, V, -Qg);
 #pragma unroll
             for (int v = 0; v < LV; ++v)
-                Js[v] = k > 0 ? Js[v] + (Xk[v] - Xg[v]) * QE[v] : (T)0;
+                Js[v] = k > 0 ? Js[v] + E[v] * QE[v] : (T)0;
             if (BOX) {
 #pragma unroll
                 for (int v = 0; v < 4; ++v) {  // x_{k+1}'s
