@@ -18,8 +18,8 @@
 // LDS round trip and a barrier each), as in the M-split rollout: one
 // wavefront pair per candidate took the same chain for a single candidate.
 // 14-DoF chain, T = 50, p = 10, FP32, 4096 candidates: 236 us with a workgroup
-// per candidate on the vector ALUs, 44 us here (65536: 3.1 ms and 0.47 ms); 64
-// candidates with five Adam steps: 235 and 220 us.
+// per candidate on the vector ALUs, 45 us here (65536, in blocks: 3.1 ms and 0.47
+// ms); 64 candidates with five Adam steps: 236 and 228 us.
 // Products with B_d per knot instead of per step, blended (41 us, 202 us), lost
 // accuracy: see drive.  Errors against 64 bits, relative to the per-candidate
 // kernel's (FP32, rms over horizons of 20 to 200): gradient 0.89 to 1.00 and cost
@@ -48,8 +48,8 @@ inline LinAdjPlan lin_adj_layout(int NT, int UT, int T, int p, bool refine, int 
     g.nblk = full ? 1 : (T + S - 1) / S;
     const size_t slot = (size_t)NT * 256, kn = (size_t)p * UT * 256;
     size_t o = 0;
-    // full: x_0 .. x_{T-1}; else the blocks' first states, one block, a ring of two
-    g.oX = o; o += slot * (full ? (size_t)T : (size_t)g.nblk + S + 2);
+    // full: x_0 .. x_{T-1}; else the blocks' first states and one block
+    g.oX = o; o += slot * (full ? (size_t)T : (size_t)g.nblk + S);
     g.oL = o; o += 2 * slot;
     g.oD = o; o += 2 * slot;
     g.oU = o; o += kn;
@@ -487,7 +487,9 @@ __global__ __launch_bounds__(64 * (NT + UT)) void adjoint_linear_kernel(
                 },
                 add);
         } else {
-            T *ring = slot(G.nblk + G.S), *chk = slot(0);
+            // the states between the blocks' first ones go through lambda's ring,
+            // idle until the barrier that ends this pass
+            T *ring = lam_at(0), *chk = slot(0);
             int q = 0;
             XT = march(
                 0, Tn, Xs, chk,
